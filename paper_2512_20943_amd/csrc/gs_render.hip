@@ -1,7 +1,9 @@
 // Tile compositing: forward and backward (the splatting renderer AirGS cites
 // in Sec. II; every training view and every delivered view runs it).
 //
-// One 64-lane wave (one workgroup) per 16x16 tile.  Lane l owns pixel
+// Large launches: one 64-lane wave (one workgroup) per 16x16 tile; smaller
+// ones: four waves per tile, one per 8x8 quadrant (see the quadrant kernels).
+// With one wave per tile, lane l owns pixel
 // (l & 7, l >> 3) of each of the tile's four 8x8 quadrants ("slots"), so a
 // slot is a compact 64-pixel block.  The tile's instance list is walked in
 // batches staged in LDS (the forward one record per lane, the backward one
@@ -27,6 +29,8 @@
 // A second kernel sums
 // each (view, Gaussian)'s rows, which that order keeps contiguous: no
 // floating-point atomics, and the result does not depend on scheduling.
+#include <algorithm>
+
 #include "gs_internal.h"
 
 namespace gs {
@@ -114,6 +118,19 @@ __device__ __forceinline__ uint32_t quadrant_mask(float4 s0, float4 s1, float4 s
     if (box_min_q(A, C, r1, r2, dA, dC, u0, u0 + 7.f, v0, v0 + 7.f) <= thr) m |= 1u << w;
   }
   return m;
+}
+
+// The same for the one quadrant at (ox, oy).
+__device__ __forceinline__ bool quadrant_hit(float4 s0, float4 s1, float4 s2, float ox, float oy) {
+  const float A = s0.z, B = s0.w, C = s1.x, dq = s2.z, op = s1.y;
+  // alpha >= 1/255  <=>  q <= 2 ln(255 opacity)
+  const float qmax = 2.f * (kLn255 + __logf(op));
+  const float thr = qmax + 2e-4f * fabsf(qmax) + 1e-3f;
+  // hardware reciprocals: their error is far inside the threshold's margin
+  const float iA = __builtin_amdgcn_rcpf(A), iC = __builtin_amdgcn_rcpf(C);
+  const float r1 = B * iA, r2 = B * iC, dA = dq * iA, dC = dq * iC;
+  const float u0 = ox - s0.x, v0 = oy - s0.y;
+  return thr > 0.f && box_min_q(A, C, r1, r2, dA, dC, u0, u0 + 7.f, v0, v0 + 7.f) <= thr;
 }
 
 // Bits 0 and 1 set when some pixel of the quadrant at (ox, oyq), resp.
@@ -483,6 +500,241 @@ __global__ __launch_bounds__(64) void k_render_fwd_l1(
                                       n_contrib + pix * v, nullptr, &o, cnt);
 }
 
+// ---------------------------------------------------------------- forward,
+// one wave per quadrant
+// The forward for launches that do not fill the chip many times over.  A
+// tile is a workgroup of four waves, one per 8x8 quadrant, a pixel per lane.
+// Each wave stages the whole list itself, 64 entries at a time, and keeps
+// only those its own quadrant needs, packed, so its walk is a counted loop
+// without a test per entry; the waves share nothing until the end, so there
+// is no barrier in the loop and a quadrant whose pixels have all stopped
+// ends alone.  The next batch's records are loaded before the current one is
+// walked.  Every pixel sees the same entries with the same arithmetic as in
+// render_tile_fwd: bit-identical outputs, the L1 sums included.
+//
+// What bounds it: with few tiles the serial chain of the longest list, so
+// the entries are evaluated kQuadGroup at a time (their alphas are
+// independent, only the transmittance updates are serial); with many the
+// issue of vector instructions (19 per evaluated pair and an exp2 at a third
+// of their rate), so the lanes that still composite are a scalar mask and
+// not a sign of T, and the quadrant and the need for the alpha cap are
+// compile-time variants of the walk.  A tile's four waves load and stage
+// each record four times, which the one-wave kernel does once.
+constexpr int kQuadGroup = 2;
+constexpr int kQuadPad = 3;  // padding slots (the backward takes four at a time)
+constexpr int kQuadSlots = 64 + kQuadPad;
+
+struct QuadStage {  // one wave's packed entries
+  float4 a[kQuadSlots];
+  float4 b[kQuadSlots];
+  float4 c[kQuadSlots];  // blue, position in the tile list (int bits), unused
+};
+
+// Orders a wave's own LDS writes before its later reads and the other way
+// round (LDS is in order within a wave; this keeps the compiler from moving
+// them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Stages the record of each lane with `hit` at its slot, and after the last
+// one the padding: entries whose alpha is 0 everywhere.
+__device__ __forceinline__ void quad_stage(QuadStage& st, float4 q0, float4 q1, float4 q2,
+                                           bool hit, int slot, int count, int pos) {
+  const int lane = threadIdx.x & 63;
+  if (hit) {
+    const Rec rr = make_rec(q0, q1, q2);
+    st.a[slot] = rr.a;
+    st.b[slot] = rr.b;
+    *reinterpret_cast<float2*>(&st.c[slot]) = make_float2(rr.c.x, __int_as_float(pos));
+  }
+  if (lane < kQuadPad) {
+    st.a[count + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+    st.b[count + lane] = make_float4(0.f, -__builtin_inff(), 0.f, 0.f);
+    *reinterpret_cast<float2*>(&st.c[count + lane]) = make_float2(0.f, 0.f);
+  }
+}
+
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// One pixel of the quadrant kernels: transmittance, colour sums, last
+// composited list position; live (wave-uniform) holds the lanes that still
+// composite.
+struct QuadPixel {
+  float T, c0, c1, c2;
+  int last;
+  unsigned long long live;
+};
+
+// Composites the wave's `count` packed entries front to back.  QX, QY: the
+// quadrant's column and row, known at compile time so that the left and
+// upper ones save a subtraction; CLAMP: some staged opacity could reach the
+// alpha cap.
+template <int QX, int QY, bool CLAMP>
+__device__ __forceinline__ void quad_walk(const QuadStage& st, int count, float fx0, float fy0,
+                                          QuadPixel& px) {
+  for (int i0 = 0; i0 < count && px.live != 0; i0 += kQuadGroup) {
+    float alpha[kQuadGroup], r[kQuadGroup], g[kQuadGroup];
+#pragma unroll
+    for (int i = 0; i < kQuadGroup; ++i) {
+      const float4 ra = st.a[i0 + i], rb = st.b[i0 + i];
+      r[i] = rb.z;
+      g[i] = rb.w;
+      // differences are formed as in render_tile_fwd
+      const float dxl = ra.x - fx0, dyt = ra.y - fy0;
+      const float dx = QX ? dxl - 8.f : dxl, dy = QY ? dyt - 8.f : dyt;
+      const float ea = eval_ea(ra, row_q(rb, dy), dx, dy);
+      alpha[i] = CLAMP ? fminf(kAlphaMax, ea) : ea;
+    }
+    // keeps the group's alphas in front of the serial part, instead of sunk
+    // into it behind its branches
+#pragma unroll
+    for (int i = 0; i < kQuadGroup; ++i) asm volatile("" : "+v"(alpha[i]));
+#pragma unroll
+    for (int i = 0; i < kQuadGroup; ++i) {
+      const unsigned long long use =
+          px.live & __builtin_amdgcn_ballot_w64(alpha[i] >= kAlphaMin);
+      if (use == 0) continue;  // 1 % faster at full size than without
+      const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
+      const float Tn = px.T * (1.f - alpha[i]);
+      const unsigned long long stop = use & __builtin_amdgcn_ballot_w64(Tn < kTStop);
+      const unsigned long long cm = use & ~stop;
+      const bool comp = __builtin_amdgcn_inverse_ballot_w64(cm);
+      px.live &= ~stop;
+      const float wt = comp ? alpha[i] * px.T : 0.f;
+      px.c0 = fmaf(r[i], wt, px.c0);
+      px.c1 = fmaf(g[i], wt, px.c1);
+      px.c2 = fmaf(c.x, wt, px.c2);
+      px.T = comp ? Tn : px.T;  // a stopping pixel keeps its transmittance
+      px.last = comp ? __float_as_int(c.y) : px.last;
+    }
+  }
+}
+
+template <bool CLAMP>
+__device__ __forceinline__ void quad_walk_of(int wave, const QuadStage& st, int count, float fx0,
+                                             float fy0, QuadPixel& px) {
+  switch (wave) {
+    case 0: quad_walk<0, 0, CLAMP>(st, count, fx0, fy0, px); break;
+    case 1: quad_walk<1, 0, CLAMP>(st, count, fx0, fy0, px); break;
+    case 2: quad_walk<0, 1, CLAMP>(st, count, fx0, fy0, px); break;
+    default: quad_walk<1, 1, CLAMP>(st, count, fx0, fy0, px); break;
+  }
+}
+
+// One tile by a workgroup of four waves; the arguments are those of
+// render_tile_fwd.
+template <bool L1>
+__device__ __forceinline__ void render_tile_quads(QuadStage (&sh)[4],
+                                                  const float4* __restrict__ sv,
+                                                  const uint32_t* __restrict__ vals, uint2 rg,
+                                                  int tx, int ty, int W, int H, float bg0,
+                                                  float bg1, float bg2, float* __restrict__ image,
+                                                  float* __restrict__ final_T,
+                                                  int32_t* __restrict__ n_contrib,
+                                                  const L1Out* l1 = nullptr) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int xl = tx * kTile + (lane & 7), yl = ty * kTile + (lane >> 3);
+  const int x = xl + 8 * (wave & 1), y = yl + 8 * (wave >> 1);
+  const float fx0 = (float)xl, fy0 = (float)yl;
+  const float ox = (float)(tx * kTile + 8 * (wave & 1));
+  const float oy = (float)(ty * kTile + 8 * (wave >> 1));
+  const bool inside = x < W && y < H;
+  QuadPixel px{1.f, 0.f, 0.f, 0.f, 0, __builtin_amdgcn_ballot_w64(inside)};
+  uint32_t e = rg.x + (uint32_t)lane;
+  float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0, q2 = q0;
+  auto load = [&](uint32_t g) {
+    const float4* r = sv + kSplatF4 * (size_t)g;
+    q0 = r[0];
+    q1 = r[1];
+    q2 = r[2];
+  };
+  if (e < rg.y) load(vals[e]);
+  uint32_t gn = e + 64 < rg.y ? vals[e + 64] : 0u;  // the next batch's id
+  QuadStage& st = sh[wave];
+  for (uint32_t b0 = rg.x; b0 < rg.y && px.live != 0; b0 += 64, e += 64) {
+    const bool hit = e < rg.y && quadrant_hit(q0, q1, q2, ox, oy);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    const int count = (int)__popcll(m);
+    quad_stage(st, q0, q1, q2, hit, lanes_below(m), count, (int)(e - rg.x) + 1);
+    // exp2(log2(opacity) + x), x <= 0, stays below the cap at these opacities
+    const bool clamp = __builtin_amdgcn_ballot_w64(hit && !(q1.y < 0.98f)) != 0;
+    if (e + 64 < rg.y) load(gn);
+    gn = e + 128 < rg.y ? vals[e + 128] : 0u;
+    wave_lds_fence();
+    if (clamp)
+      quad_walk_of<true>(wave, st, count, fx0, fy0, px);
+    else
+      quad_walk_of<false>(wave, st, count, fx0, fy0, px);
+    wave_lds_fence();
+  }
+  const size_t pix = (size_t)W * H;
+  float4 dabs = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (inside) {
+    const size_t p = (size_t)y * W + x;
+    const float o[3] = {px.c0 + px.T * bg0, px.c1 + px.T * bg1, px.c2 + px.T * bg2};
+    if (!L1 || image) {
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) image[ch * pix + p] = o[ch];
+    }
+    if constexpr (L1) {
+      const float iv = l1->inv_count;
+      float d[3];
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        d[ch] = o[ch] - l1->target[ch * pix + p];
+        l1->grad[ch * pix + p] = d[ch] > 0.f ? iv : (d[ch] < 0.f ? -iv : 0.f);
+      }
+      dabs = make_float4(fabsf(d[0]), fabsf(d[1]), fabsf(d[2]), 0.f);
+    }
+    if (final_T) final_T[p] = px.T;
+    if (n_contrib) n_contrib[p] = px.last;
+  }
+  if constexpr (L1) {
+    // the tile's sum in render_tile_fwd's order: per lane over the quadrants,
+    // then over the lanes
+    st.a[lane] = dabs;
+    __syncthreads();
+    if (wave == 0) {
+      double l1sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float4 d = sh[w].a[lane];
+        l1sum += (double)d.x;
+        l1sum += (double)d.y;
+        l1sum += (double)d.z;
+      }
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) l1sum += __shfl_xor(l1sum, off, 64);
+      if (lane == 0) *l1->partial = l1sum;
+    }
+  }
+}
+
+template <bool L1>
+__global__ __launch_bounds__(256) void k_render_fwd_quads(
+    const float4* __restrict__ splat, int ld, const uint32_t* __restrict__ vals,
+    const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
+    float bg1, float bg2, float* __restrict__ image, float* __restrict__ final_T,
+    int32_t* __restrict__ n_contrib, const float* __restrict__ target, float* __restrict__ grad,
+    float inv_count, double* __restrict__ partial) {
+  __shared__ QuadStage sh[4];
+  const int seg = blockIdx.x;
+  const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
+  const int ty = tile / TX, tx = tile - ty * TX;
+  const size_t pix = (size_t)W * H;
+  L1Out o{nullptr, nullptr, 0.f, nullptr};
+  if constexpr (L1) o = L1Out{target + 3 * pix * v, grad + 3 * pix * v, inv_count, partial + seg};
+  render_tile_quads<L1>(sh, splat + kSplatF4 * (size_t)v * ld, vals, ranges[seg], tx, ty, W, H,
+                        bg0, bg1, bg2, image ? image + 3 * pix * v : nullptr, final_T + pix * v,
+                        n_contrib + pix * v, &o);
+}
+
 // loss += (sum of the per-tile partials) / count in two fixed-order steps:
 // workgroup b adds partials [b chunk, (b + 1) chunk) (each thread a fixed
 // stride pattern, then a tree) and stores the sum over the first of them,
@@ -537,53 +789,79 @@ __global__ __launch_bounds__(64) void k_render_fwd_usage(
 }
 
 // Per-request geometry for the batched renderer: segment base (V+1), pixel
-// base (V+1, in pixels of the packed output), width/height (V).
-__global__ void k_batch_info(const gs_camera* __restrict__ cams, int V, uint32_t* seg_base,
-                             int64_t* pix_base, int2* wh, uint32_t* queue) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  uint32_t s = 0;
-  int64_t p = 0;
-  for (int v = 0; v < V; ++v) {
-    const int W = cams[v].width, H = cams[v].height;
-    seg_base[v] = s;
-    pix_base[v] = p;
-    wh[v] = make_int2(W, H);
-    s += (uint32_t)(tiles_across(W) * tiles_across(H));
-    p += (int64_t)W * H;
+// base (V+1, in pixels of the packed output), width/height (V).  One wave,
+// 64 requests at a time.
+__global__ __launch_bounds__(64) void k_batch_info(const gs_camera* __restrict__ cams, int V,
+                                                   uint32_t* __restrict__ seg_base,
+                                                   int64_t* __restrict__ pix_base,
+                                                   int2* __restrict__ wh) {
+  const int lane = threadIdx.x;
+  uint32_t s0 = 0;
+  int64_t p0 = 0;
+  for (int v0 = 0; v0 < V; v0 += 64) {
+    const int v = v0 + lane;
+    int2 d = make_int2(0, 0);
+    if (v < V) {
+      d = make_int2(cams[v].width, cams[v].height);
+      wh[v] = d;
+    }
+    const uint32_t nt = (uint32_t)(tiles_across(d.x) * tiles_across(d.y));
+    const int64_t np = (int64_t)d.x * d.y;
+    uint32_t s = nt;
+    int64_t p = np;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t ys = __shfl_up(s, off, 64);
+      const int64_t yp = __shfl_up(p, off, 64);
+      if (lane >= off) {
+        s += ys;
+        p += yp;
+      }
+    }
+    if (v < V) {
+      seg_base[v] = s0 + s - nt;
+      pix_base[v] = p0 + p - np;
+    }
+    s0 += __shfl(s, 63, 64);
+    p0 += __shfl(p, 63, 64);
   }
-  seg_base[V] = s;
-  pix_base[V] = p;
-  *queue = 0u;
+  if (lane == 0) {
+    seg_base[V] = s0;
+    pix_base[V] = p0;
+  }
 }
 
-// Persistent multi-request renderer: each workgroup repeatedly takes the
-// next (request, tile) item from a device-wide counter until the queue is
-// drained, so requests of uneven sizes share one launch.
-__global__ __launch_bounds__(64) void k_render_persistent(
+// Multi-request renderer: a workgroup per (request, tile), so requests of
+// uneven sizes share one launch and the hardware hands tiles to the CUs as
+// they become free: 2,880 us for 207,360 tiles (63 M instances), against
+// 3,780 for a resident grid of 16 waves per CU that took tiles from a counter
+// in memory.  QUADS: four waves per tile, else one.  seg0: the launch's first
+// tile.
+template <bool QUADS>
+__global__ __launch_bounds__(QUADS ? 256 : 64) void k_render_batched(
     const float4* __restrict__ splat, int ld, const uint32_t* __restrict__ vals,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ seg_base,
-    const int64_t* __restrict__ pix_base, const int2* __restrict__ wh, int V, uint32_t total,
-    float bg0, float bg1, float bg2, float* __restrict__ images, uint32_t* __restrict__ queue) {
-  __shared__ FwdShared sh;
-  __shared__ uint32_t s_item;
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) s_item = atomicAdd(queue, 1u);
-    __syncthreads();
-    const uint32_t item = s_item;
-    if (item >= total) break;
-    int lo = 0, hi = V - 1;  // request: last v with seg_base[v] <= item
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (seg_base[mid] <= item) lo = mid; else hi = mid - 1;
-    }
-    const int2 d = wh[lo];
-    const int TX = tiles_across(d.x);
-    const int tile = (int)(item - seg_base[lo]);
-    const int ty = tile / TX, tx = tile - ty * TX;
-    render_tile_fwd<false>(sh, nullptr, splat + kSplatF4 * (size_t)lo * ld, vals, ranges[item],
-                           tx, ty, d.x, d.y, bg0, bg1, bg2, images + 3 * pix_base[lo], nullptr,
-                           nullptr, nullptr);
+    const int64_t* __restrict__ pix_base, const int2* __restrict__ wh, int V, uint32_t seg0,
+    float bg0, float bg1, float bg2, float* __restrict__ images) {
+  const uint32_t item = seg0 + blockIdx.x;
+  int lo = 0, hi = V - 1;  // request: last v with seg_base[v] <= item
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (seg_base[mid] <= item) lo = mid; else hi = mid - 1;
+  }
+  const int2 d = wh[lo];
+  const int TX = tiles_across(d.x);
+  const int tile = (int)(item - seg_base[lo]);
+  const int ty = tile / TX, tx = tile - ty * TX;
+  const float4* sv = splat + kSplatF4 * (size_t)lo * ld;
+  float* image = images + 3 * pix_base[lo];
+  if constexpr (QUADS) {
+    __shared__ QuadStage sh[4];
+    render_tile_quads<false>(sh, sv, vals, ranges[item], tx, ty, d.x, d.y, bg0, bg1, bg2, image,
+                             nullptr, nullptr);
+  } else {
+    __shared__ FwdShared sh;
+    render_tile_fwd<false>(sh, nullptr, sv, vals, ranges[item], tx, ty, d.x, d.y, bg0, bg1, bg2,
+                           image, nullptr, nullptr, nullptr);
   }
 }
 
@@ -936,6 +1214,21 @@ __global__ __launch_bounds__(256) void k_grad_gather(int n, int ld, int V,
 
 }  // namespace
 
+namespace {
+// Most tiles of a forward launch that runs one wave per quadrant.  render_fwd
+// stage with the L1 term, one wave per tile -> four, in us: 64 tiles 372 ->
+// 84, 1,200 tiles (0.65 M instances) 200 -> 71, 3,600 tiles (1.1 M) 148 ->
+// 93, 10,880 tiles 257 -> 202, 21,760 tiles 428 -> 385, 32,640 tiles 610 ->
+// 582, 54,400 tiles 958 -> 956, 108,800 tiles (32 M) 1,893 -> 1,898.  Where
+// they are equal the fourfold staging is work for nothing (the backward that
+// follows such a launch ran 3 % slower), so the line lies below that.
+constexpr int kQuadFwdTiles = 36000;
+// The same for a batch of requests (no backward follows, uneven sizes): 14,160
+// tiles 364 -> 279, 30,720 tiles 532 -> 513, 66,000 tiles 1,102 -> 1,072,
+// 134,400 tiles 1,955 -> 2,073.
+constexpr int64_t kQuadBatchTiles = 66000;
+}  // namespace
+
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
                        const float bg[3], float* image, float* final_T, int32_t* n_contrib,
                        uint32_t* usage, hipStream_t s) {
@@ -954,6 +1247,12 @@ void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, g_work);
+  else if (blocks <= kQuadFwdTiles)
+    hipLaunchKernelGGL(k_render_fwd_quads<false>, dim3(blocks), dim3(256), 0, s,
+                       reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
+                       reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
+                       bg[2], image, final_T, n_contrib, (const float*)nullptr, (float*)nullptr,
+                       0.f, (double*)nullptr);
   else
     hipLaunchKernelGGL(k_render_fwd<false>, dim3(blocks), dim3(64), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
@@ -982,6 +1281,12 @@ void launch_render_fwd_l1(const gs_projected& proj, const gs_tile_lists& lists, 
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, target, grad, (float)(1.0 / count),
                        partial, g_work);
+  else if (blocks <= kQuadFwdTiles)
+    hipLaunchKernelGGL(k_render_fwd_quads<true>, dim3(blocks), dim3(256), 0, s,
+                       reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
+                       reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
+                       bg[2], image, final_T, n_contrib, target, grad, (float)(1.0 / count),
+                       partial);
   else
     hipLaunchKernelGGL(k_render_fwd_l1<false>, dim3(blocks), dim3(64), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
@@ -1006,28 +1311,22 @@ void launch_render_batched(const gs_projected& proj, const gs_tile_lists& lists,
                            const gs_camera* cams_dev, int V, int64_t total_segments,
                            const float bg[3], float* images, void* ws, hipStream_t s) {
   char* w = static_cast<char*>(ws);
-  uint32_t* queue = reinterpret_cast<uint32_t*>(w);
-  w += 256;
   uint32_t* seg_base = reinterpret_cast<uint32_t*>(w);
   w += 256 * ((((size_t)V + 1) * 4 + 255) / 256);
   int64_t* pix_base = reinterpret_cast<int64_t*>(w);
   w += 256 * ((((size_t)V + 1) * 8 + 255) / 256);
   int2* wh = reinterpret_cast<int2*>(w);
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0)
-    cus = 256;  // the grid size only tunes occupancy; the queue drains either way
-  const int64_t want = (int64_t)cus * 16;
-  const int blocks = (int)(total_segments < want ? total_segments : want);
   StageScope scope(kStRenderFwd, s);
-  hipLaunchKernelGGL(k_batch_info, dim3(1), dim3(64), 0, s, cams_dev, V, seg_base, pix_base, wh,
-                     queue);
-  if (blocks <= 0) return;
-  hipLaunchKernelGGL(k_render_persistent, dim3(blocks), dim3(64), 0, s,
-                     reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
-                     reinterpret_cast<const uint2*>(lists.ranges), seg_base, pix_base, wh, V,
-                     (uint32_t)total_segments, bg[0], bg[1], bg[2], images, queue);
+  hipLaunchKernelGGL(k_batch_info, dim3(1), dim3(64), 0, s, cams_dev, V, seg_base, pix_base, wh);
+  const bool quads = total_segments <= kQuadBatchTiles;
+  // a grid holds fewer than 2^32 threads
+  constexpr int64_t kMost = (int64_t)1 << 24;
+  for (int64_t s0 = 0; s0 < total_segments; s0 += kMost)
+    hipLaunchKernelGGL(quads ? k_render_batched<true> : k_render_batched<false>,
+                       dim3((unsigned)std::min(kMost, total_segments - s0)),
+                       dim3(quads ? 256 : 64), 0, s, reinterpret_cast<const float4*>(proj.splat),
+                       proj.ld, lists.vals, reinterpret_cast<const uint2*>(lists.ranges),
+                       seg_base, pix_base, wh, V, (uint32_t)s0, bg[0], bg[1], bg[2], images);
 }
 
 void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,

@@ -9,8 +9,7 @@
 // a stream and growable device buffers, and renders a batch with the
 // library's own calls: one apply per distinct frame, one projection per
 // frame group into consecutive view slots, one joint binning over all
-// requests, and one persistent compositing launch over the shared (request,
-// tile) queue (a batch of one takes the single-view compositing call, the
+// requests, and one compositing launch over all (request, tile) pairs (a batch of one takes the single-view compositing call, the
 // same image bit for bit).  While arrivals are sparse, a lone request on an
 // idle server is rendered on the scheduler's thread by a renderer of its
 // own, which saves the wake-up of a worker thread.  The plain mode serves

@@ -5,7 +5,7 @@
   the forward render (``gs_opts.usage``).
 * ``PruningSweep`` builds the dense pruning-level space S_t^d of one frame:
   for each level it applies the pruned update, renders all evaluation views
-  of all levels in one persistent batched launch, and measures quality as
+  of all levels in one batched launch, and measures quality as
   the PSNR of each level's renders against the frame's reference views
   (squared errors reduced on the device) and size as the bytes of the kept
   update texels.

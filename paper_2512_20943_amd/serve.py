@@ -12,13 +12,13 @@ viewpoint, resolution).  The server
   batch;
 * runs each batch on its worker's own HIP stream: one apply per distinct
   frame, projection per frame group, one joint bin + sort over all requests
-  (the request is the high part of the segment id), and one persistent
-  render launch over the shared (request, tile) queue;
+  (the request is the high part of the segment id), and one render launch
+  over all (request, tile) pairs;
 * keeps two workers so one batch's projection and sorting overlap another
   batch's rendering on the device;
 * renders a batch of one request with the plain kernel sequence (the same
-  image bit for bit; it skips the batch bookkeeping launch and the shared
-  queue, which only pay off when requests share a launch);
+  image bit for bit; it skips the batch bookkeeping launch, which only pays
+  off when requests share a launch);
 * when every worker is idle, a single request is waiting and arrivals are
   sparse (the observed mean gap between arrivals is more than 2.5 times
   the observed render time of a lone request), renders it on the
