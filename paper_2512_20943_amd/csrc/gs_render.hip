@@ -907,6 +907,25 @@ __device__ __forceinline__ int wave_max(int x) {
   return x;
 }
 
+// One instance's gradient row from its nine sums over the tile's pixels:
+// mom = (gp t, gp dy, gp t^2, gp t dy, gp dy^2, gp, colour gradients) with
+// gp = dL/dpower, r1 = B / A, and iop = 1 / opacity.
+__device__ __forceinline__ void write_grad_row(float* __restrict__ dst, const float (&mom)[9],
+                                               float r1, float A, float B, float C, float iop) {
+  // back from (t, dy) to (dx, dy) with dx = t - r1 dy: the sums of gp dx,
+  // dx^2 and dx dy
+  const float m_y = mom[1], m_yy = mom[4];
+  const float m_x = fmaf(-r1, m_y, mom[0]);
+  const float m_xx = fmaf(-r1, fmaf(-r1, m_yy, 2.f * mom[3]), mom[2]);
+  const float m_xy = fmaf(-r1, m_yy, mom[3]);
+  // power = -(A dx^2 + C dy^2)/2 - B dx dy with dx = px - x, dy = py - y
+  const float out[9] = {-(A * m_x + B * m_y), -(B * m_x + C * m_y), -0.5f * m_xx, -m_xy,
+                        -0.5f * m_yy,         mom[5] * iop,         mom[6],       mom[7],
+                        mom[8]};
+#pragma unroll
+  for (int cc = 0; cc < 9; ++cc) dst[cc] = out[cc];
+}
+
 // With COUNT, the tile's work tallies (entries staged and visited, slot
 // evaluations, pairs inside the pixel's prefix with alpha >= 1/255) are
 // added to cnt[4..7].
@@ -1075,27 +1094,7 @@ __global__ __launch_bounds__(64) void k_render_bwd(
           const float* r4 = acc + k * kAccStride + 4 * cc;
           mom[cc] = (r4[0] + r4[1]) + (r4[2] + r4[3]);
         }
-        // back from (t, dy) to (dx, dy) with dx = t - r1 dy: the sums of gp
-        // dx, dx^2 and dx dy
-        const float r1 = sh.a[k].w;
-        const float m_t = mom[0], m_tt = mom[2], m_ty = mom[3], m_yy = mom[4];
-        mom[0] = fmaf(-r1, mom[1], m_t);
-        mom[2] = fmaf(-r1, fmaf(-r1, m_yy, 2.f * m_ty), m_tt);
-        mom[3] = fmaf(-r1, m_yy, m_ty);
-        // power = -(A dx^2 + C dy^2)/2 - B dx dy with dx = px - x, dy = py - y
-        const float A = sh.A[k], B = sh.c[k].z, C = sh.c[k].w;
-        float out[9];
-        out[0] = -(A * mom[0] + B * mom[1]);
-        out[1] = -(B * mom[0] + C * mom[1]);
-        out[2] = -0.5f * mom[2];
-        out[3] = -mom[3];
-        out[4] = -0.5f * mom[4];
-        out[5] = mom[5] * sh.c[k].y;
-        out[6] = mom[6];
-        out[7] = mom[7];
-        out[8] = mom[8];
-#pragma unroll
-        for (int cc = 0; cc < 9; ++cc) dst[cc] = out[cc];
+        write_grad_row(dst, mom, sh.a[k].w, sh.A[k], sh.c[k].z, sh.c[k].w, sh.c[k].y);
       }
     }
   }
@@ -1112,6 +1111,225 @@ __global__ __launch_bounds__(64) void k_render_bwd(
       atomicAdd(cnt + kWkBwdStaged, (unsigned long long)wk_staged);
       atomicAdd(cnt + kWkBwdVisits, (unsigned long long)wk_visits);
       atomicAdd(cnt + kWkBwdSlots, (unsigned long long)wk_slots);
+      atomicAdd(cnt + kWkBwdUsed, wk_used);
+    }
+  }
+}
+
+// ---------------------------------------------------------------- backward,
+// one wave per quadrant
+// The backward for launches with few tiles: a tile is a workgroup of four
+// waves, one per quadrant, which walk the same batches of 64 entries back to front, each over the packed entries its own
+// quadrant needs, four at a time (their alphas, reciprocals and colour
+// products are independent; the transmittance and the colour behind are
+// serial).  A wave sums the four entries' nine values over its 64 pixels
+// together and stores them; after the batch's one barrier the wave whose
+// turn it is adds the quadrants' sums and writes the rows, while the others
+// go on with the next batch into the other buffer.
+constexpr int kQuadBwdGroup = 4;  // wave_sums9x4 sums four entries
+static_assert(kQuadPad >= kQuadBwdGroup - 1 && kQuadPad >= kQuadGroup - 1, "padding");
+constexpr int kQuadAcc = 9;  // odd stride: the flush reads distinct banks
+
+struct QuadBwdShared {
+  QuadStage st[4];
+  float acc[2][4][kQuadSlots * kQuadAcc];
+  int8_t slot[2][4][64];           // an entry's packed slot in a quadrant, or -1
+  unsigned long long seen[2][4];   // with COUNT, entries a quadrant evaluated
+  int wmax[4];
+};
+
+// Each half of the wave gets one of two values' sums over both halves: lanes
+// below 32 that of lo, the others that of hi (a swap and an add per pair).
+__device__ __forceinline__ float pair_halves(float lo, float hi) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false,
+                                                  false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+// The same within each half: rows 0 and 2 get lo's sum over rows (0, 1) and
+// (2, 3), rows 1 and 3 that of hi.
+__device__ __forceinline__ float pair_rows(float lo, float hi) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false,
+                                                  false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+// Sums over the wave of nine values of four entries, scattered: row r of the
+// wave ends up with entry {0, 2, 1, 3}[r], its lanes with the values as in
+// row_sums9.  19 instructions per entry, against 22 for the row sums of one
+// entry alone.
+__device__ __forceinline__ float wave_sums9x4(const float (&x)[4][9], bool u1, bool u0) {
+  float y[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c)
+    y[c] = pair_rows(pair_halves(x[0][c], x[1][c]), pair_halves(x[2][c], x[3][c]));
+  return row_sums9(y, u1, u0);
+}
+
+template <bool COUNT>
+__global__ __launch_bounds__(256) void k_render_bwd_quads(
+    const float4* __restrict__ splat, int ld, const uint32_t* __restrict__ vals,
+    const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
+    float bg1, float bg2, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
+    const float* __restrict__ dL_dimage, float* __restrict__ rows,
+    unsigned long long* __restrict__ cnt) {
+  __shared__ QuadBwdShared sh;
+  const int seg = blockIdx.x;
+  const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
+  const int ty = tile / TX, tx = tile - ty * TX;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint2 rg = ranges[seg];
+  const float4* sv = splat + kSplatF4 * (size_t)v * ld;
+  const size_t pix = (size_t)W * H;
+  const int xl = tx * kTile + (lane & 7), yl = ty * kTile + (lane >> 3);
+  const int x = xl + 8 * (wave & 1), y = yl + 8 * (wave >> 1);
+  const float fx0 = (float)xl, fy0 = (float)yl;
+  const float offx = (wave & 1) ? 8.f : 0.f, offy = (wave >> 1) ? 8.f : 0.f;
+  const float ox = (float)(tx * kTile) + offx, oy = (float)(ty * kTile) + offy;
+  float T = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+  int nc = 0;
+  if (x < W && y < H) {
+    const size_t p = (size_t)y * W + x;
+    const float* gi = dL_dimage + 3 * pix * v;
+    T = final_T[pix * v + p];
+    nc = n_contrib[pix * v + p];
+    g0 = gi[p];
+    g1 = gi[pix + p];
+    g2 = gi[2 * pix + p];
+  }
+  // dL/dcolour . (the colour composited behind the current entry)
+  float S = g0 * bg0 + g1 * bg1 + g2 * bg2;
+  const int wmax = __builtin_amdgcn_readfirstlane(wave_max(nc));
+  if (lane == 0) sh.wmax[wave] = wmax;
+  __syncthreads();
+  const int jmax = __builtin_amdgcn_readfirstlane(
+      max(max(sh.wmax[0], sh.wmax[1]), max(sh.wmax[2], sh.wmax[3])));
+  // where the sums of an entry end up (wave_sums9x4): its value, and the
+  // lanes that store one
+  const bool u3 = lane & 8, u2 = lane & 4, u1 = lane & 2, u0 = lane & 1;
+  const int acc_lane = (lane & 32 ? (lane & 16 ? 3 : 1) : (lane & 16 ? 2 : 0)) * kQuadAcc +
+                       (u0 ? 8 : 4 * (int)u1 + 2 * (int)u2 + (int)u3);
+  const bool acc_writer = !u0 || (lane & 15) == 1;
+  QuadStage& st = sh.st[wave];
+  // lane k holds the record of entry lo + k of the batch that ends at hi
+  float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0, q2 = q0, q3 = q0;
+  auto load = [&](uint32_t g) {
+    const float4* r = sv + kSplatF4 * (size_t)g;
+    q0 = r[0];
+    q1 = r[1];
+    q2 = r[2];
+    q3 = r[3];
+  };
+  auto id_of = [&](int hi) {  // this lane's entry in the batch that ends at hi
+    const int lo = max(hi - 64, 0);
+    return lo + lane < hi ? vals[rg.x + (uint32_t)(lo + lane)] : 0u;
+  };
+  if (jmax > 0) load(id_of(jmax));
+  uint32_t gn = jmax > 64 ? id_of(jmax - 64) : 0u;
+  int buf = 0, turn = 0;
+  unsigned long long wk_staged = 0, wk_visits = 0, wk_slots = 0, wk_used = 0;
+  for (int hi = jmax; hi > 0; hi -= 64, buf ^= 1, turn = (turn + 1) & 3) {
+    const int lo = max(hi - 64, 0);
+    const bool have = lo + lane < hi;
+    const bool hit = have && lo + lane < wmax && quadrant_hit(q0, q1, q2, ox, oy);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    const int count = (int)__popcll(m);
+    // packed back to front
+    const int slot = count - 1 - lanes_below(m);
+    quad_stage(st, q0, q1, q2, hit, slot, count, lo + lane);
+    sh.slot[buf][wave][lane] = (int8_t)(hit ? slot : -1);
+    // what the flush of this batch needs of the records, kept while the next
+    // batch's are loaded
+    const float fA = q0.z, fB = q0.w, fC = q1.x;
+    const float fr1 = fB * __builtin_amdgcn_rcpf(fA), fiop = __builtin_amdgcn_rcpf(q1.y);
+    const uint32_t frow = instance_row(q3, tx, ty);
+    if (hi > 64) load(gn);
+    gn = hi > 128 ? id_of(hi - 128) : 0u;
+    wave_lds_fence();
+    if constexpr (COUNT) {
+      wk_slots += (unsigned long long)count;
+      if (lane == 0) sh.seen[buf][wave] = m;
+    }
+    float* acc = sh.acc[buf][wave];
+    for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
+      float au[kQuadBwdGroup], ra[kQuadBwdGroup], gc[kQuadBwdGroup], t[kQuadBwdGroup], dy[kQuadBwdGroup];
+      bool clamped[kQuadBwdGroup];
+      float gr[kQuadBwdGroup][9];
+#pragma unroll
+      for (int i = 0; i < kQuadBwdGroup; ++i) {
+        const float4 a = st.a[i0 + i], b = st.b[i0 + i];
+        const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
+        const float dx = (a.x - fx0) - offx;
+        dy[i] = (a.y - fy0) - offy;
+        t[i] = fmaf(a.w, dy[i], dx);
+        const float ea =
+            __builtin_amdgcn_exp2f(fmaf(a.z * t[i], t[i], fmaf(b.x, dy[i] * dy[i], b.y)));
+        const float alpha = fminf(kAlphaMax, ea);
+        const bool use = __float_as_int(c.y) < nc && alpha >= kAlphaMin;
+        clamped[i] = !(ea < kAlphaMax);
+        if constexpr (COUNT) wk_used += (unsigned long long)__popcll(__ballot(use));
+        au[i] = use ? alpha : 0.f;
+        ra[i] = __builtin_amdgcn_rcpf(1.f - au[i]);
+        gc[i] = fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z));
+      }
+#pragma unroll
+      for (int i = 0; i < kQuadBwdGroup; ++i) {
+        T = T * ra[i];
+        const float wt = au[i] * T;
+        const float gcb = gc[i] - S;
+        const float gp = clamped[i] ? 0.f : wt * gcb;
+        const float pt = gp * t[i];
+        gr[i][0] = pt;
+        gr[i][1] = gp * dy[i];
+        gr[i][2] = pt * t[i];
+        gr[i][3] = pt * dy[i];
+        gr[i][4] = gr[i][1] * dy[i];
+        gr[i][5] = gp;
+        gr[i][6] = g0 * wt;
+        gr[i][7] = g1 * wt;
+        gr[i][8] = g2 * wt;
+        S = fmaf(au[i], gcb, S);
+      }
+      // the padding's sums go to slots that no entry has
+      const float rs = wave_sums9x4(gr, u1, u0);
+      if (acc_writer) acc[i0 * kQuadAcc + acc_lane] = rs;
+    }
+    __syncthreads();
+    if constexpr (COUNT) {
+      if (wave == 0) {
+        wk_staged += (unsigned long long)(hi - lo);
+        wk_visits += (unsigned long long)__popcll(sh.seen[buf][0] | sh.seen[buf][1] |
+                                                  sh.seen[buf][2] | sh.seen[buf][3]);
+      }
+    }
+    if (wave == turn && have) {
+      float mom[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int at = sh.slot[buf][w][lane];
+        if (at >= 0) {
+          const float* a = sh.acc[buf][w] + at * kQuadAcc;
+#pragma unroll
+          for (int cc = 0; cc < 9; ++cc) mom[cc] += a[cc];
+        }
+      }
+      write_grad_row(rows + (size_t)frow * kRowFloats, mom, fr1, fA, fB, fC, fiop);
+    }
+  }
+  // entries behind every pixel's last contributor carry zero gradient
+  const int n_entries = (int)(rg.y - rg.x);
+  for (int j = jmax + (int)threadIdx.x; j < n_entries; j += 256) {
+    const uint32_t g = vals[rg.x + (uint32_t)j];
+    float* dst = rows + (size_t)instance_row(sv[kSplatF4 * (size_t)g + 3], tx, ty) * kRowFloats;
+#pragma unroll
+    for (int cc = 0; cc < 9; ++cc) dst[cc] = 0.f;
+  }
+  if constexpr (COUNT) {
+    if (lane == 0) {
+      atomicAdd(cnt + kWkBwdStaged, wk_staged);
+      atomicAdd(cnt + kWkBwdVisits, wk_visits);
+      atomicAdd(cnt + kWkBwdSlots, wk_slots);
       atomicAdd(cnt + kWkBwdUsed, wk_used);
     }
   }
@@ -1227,6 +1445,14 @@ constexpr int kQuadFwdTiles = 36000;
 // tiles 364 -> 279, 30,720 tiles 532 -> 513, 66,000 tiles 1,102 -> 1,072,
 // 134,400 tiles 1,955 -> 2,073.
 constexpr int64_t kQuadBatchTiles = 66000;
+// Most tiles of a backward launch that runs one wave per quadrant.  There an
+// entry's sums are formed per quadrant and not once per tile, which costs 1.8
+// times the instructions, so the line lies where the one-wave kernel's serial
+// chains stop being the limit.  render_bwd stage, one wave per tile -> four,
+// in us: 64 tiles 455 -> 110, 300 tiles 130 -> 47, 1,200 tiles (0.13 M
+// instances) 73 -> 53, 1,200 tiles (0.65 M) 233 -> 161, 3,813 tiles (0.41 M)
+// 122 -> 115, 3,600 tiles (1.1 M) 209 -> 244, 10,880 tiles 398 -> 586.
+constexpr int kQuadBwdTiles = 2400;
 }  // namespace
 
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
@@ -1338,16 +1564,13 @@ void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int
   if (blocks == 0) return;
   {
     StageScope scope(kStRenderBwd, s);
-    if (g_work)
-      hipLaunchKernelGGL(k_render_bwd<true>, dim3(blocks), dim3(64), 0, s,
-                         reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
-                         reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0],
-                         bg[1], bg[2], final_T, n_contrib, dL_dimage, rows, g_work);
-    else
-      hipLaunchKernelGGL(k_render_bwd<false>, dim3(blocks), dim3(64), 0, s,
-                         reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
-                         reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0],
-                         bg[1], bg[2], final_T, n_contrib, dL_dimage, rows, nullptr);
+    const bool quads = blocks <= kQuadBwdTiles;
+    auto kernel = quads ? (g_work ? k_render_bwd_quads<true> : k_render_bwd_quads<false>)
+                        : (g_work ? k_render_bwd<true> : k_render_bwd<false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(quads ? 256 : 64), 0, s,
+                       reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
+                       reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
+                       bg[2], final_T, n_contrib, dL_dimage, rows, g_work);
   }
   const size_t nv = (size_t)proj.n * (size_t)V;
   if (nv == 0) return;

@@ -83,3 +83,38 @@ def test_batched_launch_is_the_same_above_and_below_its_limit(many_views):
     assert torch.equal(batched(cams), ref)
     for sl, c in parts(cams):
         assert torch.equal(batched(c), ref[sl])
+
+
+def test_backward_agrees_in_large_and_small_launches(many_views):
+    """Screen-space gradients per (view, Gaussian) of 40 views in one launch
+    (4,840 tiles, one wave per tile) and in parts of 10 (1,210 tiles, one
+    wave per quadrant).  Both evaluate the same pairs; a term's products are
+    rounded in another order (4 ulp) and at most 256 of them are added in
+    another tree (10 ulp), on sums whose cancellation averages below 30 in
+    norm: 14 * 30 * 2^-24 = 2.5e-5."""
+    r, g, cams, _ = many_views
+    n, V, k = g.n, 40, 10
+    c40 = cams.slice(100, V)
+    rng = np.random.default_rng(9)
+    dimg = torch.from_numpy(rng.uniform(-1, 1, (V, 3, H, W)).astype(np.float32)).cuda()
+    bg = (0.3, 0.1, 0.2)
+
+    def grads(c, d):
+        out = r.forward(g, c, bg)
+        grad = gs.Gaussians.zeros_like(g)
+        ws = r.backward(g, c, out, d, grad, bg)
+        g2 = ws[: c.V * g.ld * 48].view(torch.float32).view(c.V, g.ld, 12)[:, :n, :9]
+        return g2.clone().double(), [p.double() for p in grad.planes()]
+
+    print(f"backward split: {V} views {W}x{H}", flush=True)
+    whole, total = grads(c40, dimg)
+    summed = [torch.zeros_like(p) for p in total]
+    for v in range(0, V, k):
+        part, planes = grads(c40.slice(v, k), dimg[v:v + k].contiguous())
+        for q in range(9):
+            a, b = part[:, :, q], whole[v:v + k, :, q]
+            assert (a - b).norm() <= 2.5e-5 * b.norm(), f"column {q} of views {v}"
+        for s, p in zip(summed, planes):
+            s += p
+    for s, p in zip(summed, total):
+        assert (s - p).norm() <= 5e-5 * p.norm()
