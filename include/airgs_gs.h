@@ -326,13 +326,15 @@ gs_status gs_project(gs_ctx* ctx, const gs_gaussians* g, const gs_camera* cams_h
 
 /* Binning and depth ordering of the splatting renderer the paper cites in
  * Sec. II (its tile-based rasterizer sorts splats per 16x16 tile by depth):
- * every (visible Gaussian, tile of its
- * rectangle, or of its per-row spans when the record carries them, see
- * GS_PROJECT_TILE_SPANS) pair is an instance; instances are ordered by
- * (segment, FP32 depth, Gaussian id) with LDS-resident radix sorts that
- * run inside each view.  Reads the instance count back to the host
- * (blocking).  Returns GS_ERR_CAPACITY with lists->count = M when
- * M > lists->capacity (nothing else is written).
+ * every (visible Gaussian, tile of its rectangle, or of its per-row spans
+ * when the record carries them, see GS_PROJECT_TILE_SPANS) pair is an
+ * instance; instances are ordered by (segment, FP32 depth, Gaussian id), by
+ * per-tile lists sorted in registers for small jobs, by LDS-resident radix
+ * sorts inside each view for large ones.  The lists are the same either way;
+ * the emission order is (view, Gaussian) in the first case and (view, depth,
+ * Gaussian) in the second.  Waits for the instance count on the host.
+ * Returns GS_ERR_CAPACITY with lists->count = M when M > lists->capacity
+ * (nothing else is written).
  * Besides the lists it writes word 14 of each listed record of proj->splat
  * (the pair's first instance in emission order, also stored in
  * lists->gv_base when that is given).

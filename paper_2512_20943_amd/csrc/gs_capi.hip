@@ -426,21 +426,22 @@ gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
   GS_TRY(use_device(c));
   hipStream_t s = (hipStream_t)stream;
   lists->n_segments = nseg;
-  uint32_t* d_stats = nullptr;
-  hipError_t e = gs::bin_sort_stage1(plan, *proj, cd, ws, s, &d_stats);
-  if (e != hipSuccess) return hip_fail(c, e, "bin_sort (count)");
-  e = hipMemcpyAsync(c->pinned, d_stats, 5 * sizeof(uint32_t), hipMemcpyDeviceToHost, s);
-  if (e != hipSuccess) return hip_fail(c, e, "instance count readback");
-  e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
-  const uint32_t dmin = c->pinned[0], dmax = c->pinned[1];
-  const uint64_t M = (uint64_t)c->pinned[2] | ((uint64_t)c->pinned[3] << 32);
+  // the kernels write the totals into the context's pinned slot
+  uint32_t* stats = c->pinned;
+  for (int k = 0; k < 8; ++k) stats[k] = 0;
+  hipError_t e = hipSuccess;
+  if (proj->n > 0) {
+    e = gs::bin_sort_stage1(plan, *proj, cd, ws, stats, s);
+    if (e != hipSuccess) return hip_fail(c, e, "bin_sort (count)");
+    e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+  }
+  const uint64_t M = (uint64_t)stats[2] | ((uint64_t)stats[3] << 32);
   lists->count = (int64_t)M;
   if (M > (uint64_t)lists->capacity)
     return fail(c, GS_ERR_CAPACITY, "instance count %llu exceeds capacity %lld",
                 (unsigned long long)M, (long long)lists->capacity);
-  const uint32_t n_visible = c->pinned[4];
-  e = gs::bin_sort_stage2(plan, *proj, cd, (uint32_t)M, dmin, dmax, n_visible, *lists, ws, s);
+  e = gs::bin_sort_stage2(plan, *proj, stats, *lists, ws, s);
   if (e != hipSuccess) return hip_fail(c, e, "bin_sort (sort)");
   return GS_OK;
 }

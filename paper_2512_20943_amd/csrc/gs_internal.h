@@ -97,15 +97,15 @@ struct BinSortPlan {
 };
 size_t bin_sort_workspace_bytes(int n_views, int ld, int64_t capacity, int64_t n_segments);
 // Stage 1 reduces the visible pairs' depth-bit range and instance count
-// into 4 device words {min bits, max bits, count (u64)}; the second stage,
-// once the host has read them, depth-sorts, emits, sorts by tile and builds
-// ranges.
+// into words of host memory, stats = {min bits, max bits, count (u64),
+// visible pairs, count (low word), longest tile list where it is counted};
+// the second stage, once the host has waited for them, builds the lists.
+// With no Gaussian at all there is nothing to launch and stats is not
+// written.
 hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
-                           const gs_camera* cams_dev, void* ws, hipStream_t s,
-                           uint32_t** d_stats);
-hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj,
-                           const gs_camera* cams_dev, uint32_t M, uint32_t dmin, uint32_t dmax,
-                           uint32_t n_visible, gs_tile_lists& lists, void* ws, hipStream_t s);
+                           const gs_camera* cams_dev, void* ws, uint32_t* stats, hipStream_t s);
+hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const uint32_t* stats,
+                           gs_tile_lists& lists, void* ws, hipStream_t s);
 // render
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int n_views, int W,
                        int H, const float bg[3], float* image, float* final_T,

@@ -1,8 +1,10 @@
 // Tile binning and depth ordering.
 //
 // The order the renderer needs is, per tile segment, the instances sorted by
-// (FP32 depth, Gaussian id).  It is reached in two sorts that both use the
-// same LDS-resident LSD radix sort (stable, 8- or 9-bit digits; per digit,
+// (FP32 depth, Gaussian id).  Jobs of few (view, Gaussian) pairs count and
+// fill the tile lists directly and sort each one in registers (the direct
+// route below, plan_direct).  Large ones reach the order in two sorts that
+// both use the same LDS-resident LSD radix sort (stable, 8- or 9-bit digits; per digit,
 // per-partition counts, their scan, then LDS ranking and an LDS-staged
 // scatter with those bases; partitions are laid out XCD by XCD, so each of
 // the 8 L2s sees a contiguous range).  Both sorts run inside views: the
@@ -363,21 +365,11 @@ __global__ __launch_bounds__(kBlock) void k_scatter_pass(
 
 // ------------------------------------------------------------ binning
 // Per-view tile geometry from the device cameras, seg_base (V+1) and tx
-// (V), one view per thread with a block scan; also initialises the
-// stage-1 statistics, stats = {min bits, max bits, count lo, hi, visible}
-// (all overwritten when some pair is visible).  One block.
-__global__ __launch_bounds__(kBlock) void k_view_info(const gs_camera* __restrict__ cams, int V,
-                                                      uint32_t* __restrict__ seg_base,
-                                                      int32_t* __restrict__ txv,
-                                                      uint32_t* __restrict__ stats) {
+// (V), one view per thread with a block scan.  One block.
+__device__ __forceinline__ void view_info(const gs_camera* __restrict__ cams, int V,
+                                          uint32_t* __restrict__ seg_base,
+                                          int32_t* __restrict__ txv) {
   __shared__ uint32_t s_wave[4];
-  if (threadIdx.x == 0) {
-    stats[0] = 0xFFFFFFFFu;
-    stats[1] = 0u;
-    stats[2] = 0u;
-    stats[3] = 0u;
-    stats[4] = 0u;
-  }
   uint32_t carry = 0;
   for (int v0 = 0; v0 < V; v0 += kBlock) {
     const int v = v0 + (int)threadIdx.x;
@@ -427,6 +419,15 @@ __device__ __forceinline__ void load_run(const int32_t* __restrict__ tv,
 
 __device__ __forceinline__ bool rows_aligned(int ld, const void* a, const void* b) {
   return (ld & 3) == 0 && ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0;
+}
+
+// Zeroes zero[0, zero_n) over the whole grid (the tile ranges, cleared here
+// to save a launch of their own).
+__device__ __forceinline__ void grid_zero(uint32_t* __restrict__ zero, size_t zero_n) {
+  const size_t nthreads = (size_t)gridDim.x * gridDim.y * kBlock;
+  for (size_t z = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
+       z < zero_n; z += nthreads)
+    zero[z] = 0u;
 }
 
 // Per chunk of kCountChunk Gaussians of one view (grid x; views on grid y,
@@ -558,15 +559,6 @@ __device__ __forceinline__ void visible_keys(int n, int ld, int V,
   }
 }
 
-// Zeroes zero[0, zero_n) over the whole grid (the tile ranges, cleared here
-// to save a launch of their own).
-__device__ __forceinline__ void grid_zero(uint32_t* __restrict__ zero, size_t zero_n) {
-  const size_t nthreads = (size_t)gridDim.x * gridDim.y * kBlock;
-  for (size_t z = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
-       z < zero_n; z += nthreads)
-    zero[z] = 0u;
-}
-
 // 32-bit (view, depth) keys when they fit: view << vshift | (bits - min
 // bits), vshift the bits of the visible depth-bit range.
 __global__ __launch_bounds__(kBlock) void k_depth_keys32(int n, int ld, int V,
@@ -649,19 +641,65 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t* __restrict__ su
 
 // The end of stage 1 in one launch: block 0 reduces the chunk partials
 // into stats[0..3], blocks 1 and 2 scan the visible-pair and instance
-// counts per chunk (totals to stats[4] and stats[5]).
-__global__ __launch_bounds__(kBlock) void k_stage1_close(const uint4* __restrict__ part,
-                                                         uint32_t* __restrict__ vis,
-                                                         uint32_t* __restrict__ icnt,
-                                                         uint32_t nchunk,
-                                                         uint32_t* __restrict__ stats) {
+// counts per chunk (totals to stats[4] and stats[5]), block 3 lays out the
+// views' tiles.  stats is the context's pinned host memory: the totals need
+// no copy of their own.
+__global__ __launch_bounds__(kBlock) void k_stage1_close(
+    const uint4* __restrict__ part, uint32_t* __restrict__ vis, uint32_t* __restrict__ icnt,
+    uint32_t nchunk, uint32_t* __restrict__ stats, const gs_camera* __restrict__ cams, int V,
+    uint32_t* __restrict__ seg_base, int32_t* __restrict__ txv) {
   if (blockIdx.x == 0) {
     stats_reduce(part, (int)nchunk, stats);
+    return;
+  }
+  if (blockIdx.x == 3) {
+    view_info(cams, V, seg_base, txv);
     return;
   }
   uint32_t* a = blockIdx.x == 1 ? vis : icnt;
   const uint32_t t = block_scan_inplace<64>(a, nchunk);
   if (threadIdx.x == 0) stats[3 + blockIdx.x] = t;
+}
+
+// What the emission of one (view, Gaussian) pair needs: its first tile in
+// the view, id, rectangle width | kSpanFlag, and the per-row spans or the
+// bits of 1 / width.
+__device__ __forceinline__ uint4 emit_entry(const uint32_t* __restrict__ record_tail, uint32_t id,
+                                            uint32_t tiles_per_row) {
+  const uint2 ow = *reinterpret_cast<const uint2*>(record_tail);  // origin, width | flag
+  const uint32_t spans = record_tail[3];
+  return make_uint4((ow.x >> 16) * tiles_per_row + (ow.x & 0xFFFFu), id, ow.y,
+                    ow.y & kSpanFlag ? spans : __float_as_uint(1.f / (float)ow.y));
+}
+
+// Tile (in the view) of the pair's instance l: row by row over its spans or
+// its rectangle.
+__device__ __forceinline__ uint32_t entry_tile(const uint4& en, uint32_t tiles_per_row,
+                                               uint32_t l) {
+  uint32_t dy, dx;
+  if (en.z & kSpanFlag) {
+    // spans s_r = b_r - a_r per byte; instances before row r: p_r
+    const uint32_t m = en.w;
+    const uint32_t sp = ((m >> 4) & 0x0F0F0F0Fu) - (m & 0x0F0F0F0Fu);
+    const uint32_t p1 = sp & 0xFFu, p2 = p1 + ((sp >> 8) & 0xFFu), p3 = p2 + ((sp >> 16) & 0xFFu);
+    dy = (uint32_t)(l >= p1) + (uint32_t)(l >= p2) + (uint32_t)(l >= p3);
+    const uint32_t before = dy == 0 ? 0u : (dy == 1 ? p1 : (dy == 2 ? p2 : p3));
+    dx = ((m >> (8 * dy)) & 15u) + (l - before);
+  } else {
+    // l / width: a rectangle has at most 2^24 tiles, so the float quotient
+    // is off by at most one
+    dy = (uint32_t)((float)l * __uint_as_float(en.w));
+    int32_t r = (int32_t)(l - dy * en.z);
+    if (r < 0) {
+      --dy;
+      r += (int32_t)en.z;
+    } else if (r >= (int32_t)en.z) {
+      ++dy;
+      r -= (int32_t)en.z;
+    }
+    dx = (uint32_t)r;
+  }
+  return en.x + dy * tiles_per_row + dx;
 }
 
 // Emit (tile of the view, Gaussian id) for each tile of each depth-sorted
@@ -696,9 +734,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(uint32_t N, int ld, uint32_t vs
                                                  uint32_t* __restrict__ splat_words,
                                                  int pack) {
   __shared__ uint32_t s_pre[kBlock + 1];
-  // {first tile in its view, id, rectangle width | kSpanFlag, spans or the
-  // bits of 1 / width}, and the view's tiles per row
-  __shared__ uint4 s_ent[kBlock];
+  __shared__ uint4 s_ent[kBlock];  // emit_entry, and its view's tiles per row
   __shared__ uint32_t s_row[kBlock];
   __shared__ uint32_t s_bwave[4];
   const uint32_t base = chunk_off[blockIdx.x];
@@ -727,12 +763,8 @@ __global__ __launch_bounds__(kBlock) void k_emit(uint32_t N, int ld, uint32_t vs
   if (c > 0) {
     const uint32_t v = view_of(keys[e], vshift);
     uint32_t* rw = splat_words + ((size_t)v * ld + g) * (4 * kSplatF4) + 12;
-    const uint2 ow = *reinterpret_cast<const uint2*>(rw);  // origin, width | flag
-    const uint32_t spans = rw[3];
     const uint32_t tx = (uint32_t)txv[v];
-    s_ent[threadIdx.x] =
-        make_uint4((ow.x >> 16) * tx + (ow.x & 0xFFFFu), g, ow.y,
-                   ow.y & kSpanFlag ? spans : __float_as_uint(1.f / (float)ow.y));
+    s_ent[threadIdx.x] = emit_entry(rw, g, tx);
     s_row[threadIdx.x] = tx;
     if (part == 0) {
       if (gv_base) gv_base[(size_t)v * ld + g] = base + pre;
@@ -762,32 +794,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(uint32_t N, int ld, uint32_t vs
         f = j - base;
         if (f >= s_pre[q + 1]) ++q;  // every entry has an instance
         const uint4 en = s_ent[q];
-        const uint32_t l = f - s_pre[q];
-        uint32_t dy, dx;
-        if (en.z & kSpanFlag) {
-          // spans s_r = b_r - a_r per byte; instances before row r: p_r
-          const uint32_t m = en.w;
-          const uint32_t sp = ((m >> 4) & 0x0F0F0F0Fu) - (m & 0x0F0F0F0Fu);
-          const uint32_t p1 = sp & 0xFFu, p2 = p1 + ((sp >> 8) & 0xFFu),
-                         p3 = p2 + ((sp >> 16) & 0xFFu);
-          dy = (uint32_t)(l >= p1) + (uint32_t)(l >= p2) + (uint32_t)(l >= p3);
-          const uint32_t before = dy == 0 ? 0u : (dy == 1 ? p1 : (dy == 2 ? p2 : p3));
-          dx = ((m >> (8 * dy)) & 15u) + (l - before);
-        } else {
-          // l / w: a rectangle has at most 2^24 tiles, so the float quotient
-          // is off by at most one
-          dy = (uint32_t)((float)l * __uint_as_float(en.w));
-          int32_t r = (int32_t)(l - dy * en.z);
-          if (r < 0) {
-            --dy;
-            r += (int32_t)en.z;
-          } else if (r >= (int32_t)en.z) {
-            ++dy;
-            r -= (int32_t)en.z;
-          }
-          dx = (uint32_t)r;
-        }
-        const uint32_t tile = en.x + dy * s_row[q] + dx;
+        const uint32_t tile = entry_tile(en, s_row[q], f - s_pre[q]);
         out[k] = pack >= 0 ? (tile << pack) | en.y : tile;
         ids[k] = en.y;
       }
@@ -809,6 +816,446 @@ __global__ __launch_bounds__(kBlock) void k_emit(uint32_t N, int ld, uint32_t vs
       }
     }
   }
+}
+
+// ------------------------------------------------ tile lists, direct route
+// Every chunk of kCountChunk Gaussians of a view counts its instances per
+// tile in LDS and writes that row; the rows are scanned down each tile's
+// column and the column totals over the tiles; then each chunk writes its
+// instances straight to their lists, and each list is sorted by (depth, id)
+// in the registers of one workgroup.  Inside a chunk the order of a list's
+// entries is left to LDS atomics; the sort's keys are distinct, so the
+// result is the same list.  Against the two radix sorts these are 6 launches
+// instead of 22, and two of them, not 17, after the host has read the
+// instance count.
+constexpr int kChunkThreads = 1024;
+constexpr int kChunkTiles = 8192;  // most tiles of a view: the LDS counters
+static_assert(kCountChunk == 2 * kChunkThreads, "two Gaussians per thread");
+
+struct ChunkPairs {  // a chunk's pairs that have instances, in id order
+  uint32_t pre[kCountChunk + 1];  // first instance of each
+  uint4 ent[kCountChunk];
+  uint32_t tile[kChunkTiles];     // counters or cursors
+  uint32_t wave_n[kChunkThreads / 64], wave_c[kChunkThreads / 64];
+};
+
+// Stages chunk `chunk` of view v; returns its instance count and the number
+// of pairs in `pairs`.  With `bases` each pair's first instance in (view,
+// Gaussian) order, from `first` on, is written to its record (word 14) and
+// to gv_base.
+__device__ __forceinline__ uint32_t stage_chunk(ChunkPairs& sh, int v, uint32_t chunk, int n,
+                                                int ld, const int32_t* __restrict__ tiles,
+                                                uint32_t tx, bool bases, uint32_t first,
+                                                uint32_t* __restrict__ splat_words,
+                                                uint32_t* __restrict__ gv_base, uint32_t& pairs) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t i0 = chunk * (uint32_t)kCountChunk + 2 * threadIdx.x;
+  const int32_t* tv = tiles + (size_t)v * ld;
+  uint32_t c[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) c[k] = i0 + k < (uint32_t)n ? (uint32_t)max(tv[i0 + k], 0) : 0u;
+  const uint32_t own_n = (c[0] > 0) + (c[1] > 0), own_c = c[0] + c[1];
+  uint32_t in_n = own_n, in_c = own_c;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t yn = __shfl_up(in_n, off, 64), yc = __shfl_up(in_c, off, 64);
+    if (lane >= off) {
+      in_n += yn;
+      in_c += yc;
+    }
+  }
+  if (lane == 63) {
+    sh.wave_n[wave] = in_n;
+    sh.wave_c[wave] = in_c;
+  }
+  __syncthreads();
+  uint32_t at_n = in_n - own_n, at_c = in_c - own_c, total = 0;
+  pairs = 0;
+  for (int w = 0; w < kChunkThreads / 64; ++w) {
+    if (w < wave) {
+      at_n += sh.wave_n[w];
+      at_c += sh.wave_c[w];
+    }
+    pairs += sh.wave_n[w];
+    total += sh.wave_c[w];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (c[k] > 0) {
+      uint32_t* rw = splat_words + ((size_t)v * ld + i0 + k) * (4 * kSplatF4) + 12;
+      sh.pre[at_n] = at_c;
+      sh.ent[at_n] = emit_entry(rw, i0 + k, tx);
+      if (bases) {
+        rw[2] = first + at_c;
+        if (gv_base) gv_base[(size_t)v * ld + i0 + k] = first + at_c;
+      }
+      ++at_n;
+      at_c += c[k];
+    }
+  }
+  if (threadIdx.x == 0) sh.pre[pairs] = total;
+  return total;
+}
+
+// Calls at(tile, id) for every instance of the staged pairs, four
+// consecutive ones per thread and search.
+template <typename At>
+__device__ __forceinline__ void each_instance(const ChunkPairs& sh, uint32_t pairs,
+                                              uint32_t total, uint32_t tx, At at) {
+  for (uint32_t f0 = 4 * threadIdx.x; f0 < total; f0 += 4 * kChunkThreads) {
+    uint32_t q = 0;  // the pair of instance f0
+#pragma unroll
+    for (uint32_t step = kCountChunk / 2; step >= 1; step >>= 1)
+      if (q + step < pairs && sh.pre[q + step] <= f0) q += step;
+    uint32_t next = sh.pre[q + 1], base = sh.pre[q];
+    uint4 en = sh.ent[q];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t f = f0 + k;
+      if (f >= total) break;
+      if (f >= next) {  // every staged pair has an instance
+        ++q;
+        base = next;
+        next = sh.pre[q + 1];
+        en = sh.ent[q];
+      }
+      at(entry_tile(en, tx, f - base), en.y);
+    }
+  }
+}
+
+// The chunk of a view that workgroup blockIdx.x takes.  Consecutive
+// workgroups go to different XCDs: each XCD takes a contiguous range of the
+// view's chunks, so that in k_tile_fill one L2 gathers the words that
+// neighbouring chunks write side by side (20-view frame, 32 M instances: 494
+// -> 300 us).
+__device__ __forceinline__ uint32_t xcd_chunk() {
+  const uint32_t xc = blockIdx.x & 7;
+  return xc * (gridDim.x >> 3) + min(xc, gridDim.x & 7) + (blockIdx.x >> 3);
+}
+
+// rows[chunk of the view][tile]: instances per tile.  Grid: chunks by views.
+__global__ __launch_bounds__(kChunkThreads) void k_tile_count(
+    int n, int ld, int V, const int32_t* __restrict__ tiles, uint32_t* __restrict__ splat_words,
+    const uint32_t* __restrict__ seg_base, const int32_t* __restrict__ txv,
+    uint32_t* __restrict__ rows) {
+  __shared__ ChunkPairs sh;
+  const uint32_t chunk = xcd_chunk();
+  for (int v = blockIdx.y; v < V; v += gridDim.y) {
+    const uint32_t sb = seg_base[v], nt = seg_base[v + 1] - sb, tx = (uint32_t)txv[v];
+    for (uint32_t t = threadIdx.x; t < nt; t += kChunkThreads) sh.tile[t] = 0u;
+    uint32_t pairs;
+    const uint32_t total = stage_chunk(sh, v, chunk, n, ld, tiles, tx, false, 0u,
+                                       splat_words, nullptr, pairs);
+    __syncthreads();
+    each_instance(sh, pairs, total, tx,
+                  [&](uint32_t tile, uint32_t) { atomicAdd(&sh.tile[tile], 1u); });
+    __syncthreads();
+    uint32_t* row = rows + (size_t)gridDim.x * sb + (size_t)chunk * nt;
+    for (uint32_t t = threadIdx.x; t < nt; t += kChunkThreads) row[t] = sh.tile[t];
+    __syncthreads();
+  }
+}
+
+// Exclusive scan of each tile's column of rows over the view's chunks, in
+// place; the column total to counts[seg].  A workgroup takes 64 tiles, its
+// 16 waves a sixteenth of the chunks each.
+__global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uint32_t chunks,
+                                                       const uint32_t* __restrict__ seg_base,
+                                                       uint32_t* __restrict__ rows,
+                                                       uint32_t* __restrict__ counts) {
+  __shared__ uint32_t s_sum[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t seg = blockIdx.x * 64 + lane;
+  const uint32_t per = (chunks + 15) / 16;
+  const uint32_t k0 = min((uint32_t)wave * per, chunks), k1 = min(k0 + per, chunks);
+  uint32_t* col = nullptr;
+  uint32_t nt = 0, sum = 0;
+  if (seg < nseg) {
+    int lo = 0, hi = V - 1;  // last view whose base <= seg
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (seg_base[mid] <= seg) lo = mid; else hi = mid - 1;
+    }
+    const uint32_t sb = seg_base[lo];
+    nt = seg_base[lo + 1] - sb;
+    col = rows + (size_t)chunks * sb + (seg - sb);
+    for (uint32_t k = k0; k < k1; ++k) sum += col[(size_t)k * nt];
+  }
+  s_sum[wave][lane] = sum;
+  __syncthreads();
+  uint32_t run = 0, total = 0;
+  for (int w = 0; w < 16; ++w) {
+    if (w == wave) run = total;
+    total += s_sum[w][lane];
+  }
+  if (seg < nseg) {
+    for (uint32_t k = k0; k < k1; ++k) {
+      const uint32_t x = col[(size_t)k * nt];
+      col[(size_t)k * nt] = run;
+      run += x;
+    }
+    if (wave == 0) counts[seg] = total;
+  }
+}
+
+// Exclusive scan of the tile counts in place, in one workgroup, with their
+// sum behind the last; the longest list to *longest (host memory).
+constexpr int kScanBlock = 1024;
+
+__global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__ counts,
+                                                          uint32_t nseg,
+                                                          uint32_t* __restrict__ longest) {
+  __shared__ uint32_t s_wave[kScanBlock / 64], s_max[kScanBlock / 64];
+  constexpr uint32_t kPer = 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t carry = 0, most = 0;
+  for (uint32_t b0 = 0; b0 < nseg; b0 += kScanBlock * kPer) {
+    const uint32_t e0 = b0 + threadIdx.x * kPer;
+    uint32_t x[kPer], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      x[k] = e0 + k < nseg ? counts[e0 + k] : 0u;
+      sum += x[k];
+      most = max(most, x[k]);
+    }
+    uint32_t incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += y;
+    }
+    __syncthreads();
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t run = carry + incl - sum;
+    for (int w = 0; w < kScanBlock / 64; ++w) {
+      const uint32_t t = s_wave[w];
+      if (w < wave) run += t;
+      carry += t;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      if (e0 + k < nseg) counts[e0 + k] = run;
+      run += x[k];
+    }
+  }
+  for (int off = 32; off >= 1; off >>= 1)
+    most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+  if (lane == 0) s_max[wave] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kScanBlock / 64; ++w) most = max(most, s_max[w]);
+    counts[nseg] = carry;
+    *longest = most;
+  }
+}
+
+// Every instance's Gaussian id to its tile's list, from starts[seg] plus the
+// chunk's place in the column on.  Writes the pairs' bases too.
+__global__ __launch_bounds__(kChunkThreads) void k_tile_fill(
+    int n, int ld, int V, const int32_t* __restrict__ tiles,
+    const uint32_t* __restrict__ chunk_off, uint32_t* __restrict__ splat_words,
+    const uint32_t* __restrict__ seg_base, const int32_t* __restrict__ txv,
+    const uint32_t* __restrict__ rows, const uint32_t* __restrict__ starts,
+    uint32_t* __restrict__ vals, uint32_t* __restrict__ gv_base) {
+  __shared__ ChunkPairs sh;
+  const uint32_t chunk = xcd_chunk();
+  for (int v = blockIdx.y; v < V; v += gridDim.y) {
+    const uint32_t sb = seg_base[v], nt = seg_base[v + 1] - sb, tx = (uint32_t)txv[v];
+    const uint32_t* row = rows + (size_t)gridDim.x * sb + (size_t)chunk * nt;
+    for (uint32_t t = threadIdx.x; t < nt; t += kChunkThreads)
+      sh.tile[t] = starts[sb + t] + row[t];
+    uint32_t pairs;
+    const uint32_t total = stage_chunk(sh, v, chunk, n, ld, tiles, tx, true,
+                                       chunk_off[(size_t)v * gridDim.x + chunk],
+                                       splat_words, gv_base, pairs);
+    __syncthreads();
+    each_instance(sh, pairs, total, tx, [&](uint32_t tile, uint32_t id) {
+      vals[atomicAdd(&sh.tile[tile], 1u)] = id;
+    });
+    __syncthreads();
+  }
+}
+
+// Sort keys: depth bits over id, read as a double.  The bits of a positive
+// FP32 number below infinity are the high word of a positive double below
+// infinity, so the doubles order as the (depth, id) pairs do, and one
+// minimum and one maximum exchange a pair of keys.
+__device__ __forceinline__ double list_key(uint32_t depth, uint32_t id) {
+  return __hiloint2double((int)depth, (int)id);
+}
+
+// One instruction each: fmin and fmax would first quiet signalling NaNs,
+// which no key is.
+__device__ __forceinline__ double key_min(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double key_max(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+template <int MASK>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+  // quad permutes, half-row and row mirrors and the row rotation by 8 are
+  // DPP moves; the others go through the LDS crossbar
+  if constexpr (MASK == 1)
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);
+  else if constexpr (MASK == 2)
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true);
+  else if constexpr (MASK == 3)
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x1B, 0xF, 0xF, true);
+  else if constexpr (MASK == 7)
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true);
+  else if constexpr (MASK == 8)
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true);
+  else if constexpr (MASK == 15)
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, true);
+  else
+    return (uint32_t)__shfl_xor((int)x, MASK, 64);
+}
+
+template <int MASK>
+__device__ __forceinline__ double lane_xor(double x) {
+  return __hiloint2double((int)lane_xor<MASK>((uint32_t)__double2hiint(x)),
+                          (int)lane_xor<MASK>((uint32_t)__double2loint(x)));
+}
+
+// One step of the sorting network across threads: key r of a thread meets
+// key r (REV: key E - 1 - r) of the thread whose index differs in MASK; the
+// lower index keeps the smaller.  Masks of 64 and more exchange through LDS.
+template <int E, int T, int MASK, bool REV>
+__device__ __forceinline__ void cross_step(double (&k)[E], double* s_keys) {
+  const int tid = threadIdx.x;
+  const bool upper = (tid & (REV ? (MASK + 1) / 2 : MASK)) != 0;
+  double p[E];
+  if constexpr (MASK >= 64) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < E; ++r) s_keys[r * T + tid] = k[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < E; ++r) p[r] = s_keys[(REV ? E - 1 - r : r) * T + (tid ^ MASK)];
+  } else {
+#pragma unroll
+    for (int r = 0; r < E; ++r) p[r] = lane_xor<MASK>(k[REV ? E - 1 - r : r]);
+  }
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const double lo = key_min(k[r], p[r]), hi = key_max(k[r], p[r]);
+    k[r] = upper ? hi : lo;
+  }
+}
+
+template <int E, int T, int STRIDE>
+__device__ __forceinline__ void merge_down(double (&k)[E], double* s_keys) {
+  if constexpr (STRIDE >= E) {
+    cross_step<E, T, STRIDE / E, false>(k, s_keys);
+    merge_down<E, T, STRIDE / 2>(k, s_keys);
+  } else if constexpr (STRIDE >= 1) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      if ((r & STRIDE) == 0) {
+        const double a = k[r], b = k[r | STRIDE];
+        k[r] = key_min(a, b);
+        k[r | STRIDE] = key_max(a, b);
+      }
+    }
+    merge_down<E, T, STRIDE / 2>(k, s_keys);
+  }
+}
+
+// Bitonic sort of T * E keys, key r of thread t in place t * E + r, each
+// merge starting with the mirrored step so that every exchange ascends.
+template <int E, int T, int SIZE>
+__device__ __forceinline__ void sort_up(double (&k)[E], double* s_keys) {
+  if constexpr (SIZE <= T * E) {
+    if constexpr (SIZE > E) {
+      cross_step<E, T, SIZE / E - 1, true>(k, s_keys);
+    } else {
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        const int q = r ^ (SIZE - 1);
+        if (r < q) {
+          const double a = k[r], b = k[q];
+          k[r] = key_min(a, b);
+          k[q] = key_max(a, b);
+        }
+      }
+    }
+    merge_down<E, T, SIZE / 4>(k, s_keys);
+    sort_up<E, T, SIZE * 2>(k, s_keys);
+  }
+}
+
+template <int E, int T>
+__device__ __forceinline__ void sort_list(uint32_t* __restrict__ list, uint32_t count,
+                                          const uint32_t* __restrict__ depth,
+                                          uint64_t* __restrict__ keys, uint32_t seg,
+                                          double* s_keys) {
+  double k[E];
+  uint32_t id[E];
+  // loaded strided (coalesced): the order before the sort does not matter
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t j = (uint32_t)r * T + threadIdx.x;
+    id[r] = j < count ? list[j] : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t j = (uint32_t)r * T + threadIdx.x;
+    k[r] = j < count ? list_key(depth[id[r]], id[r]) : __builtin_inf();
+  }
+  sort_up<E, T, 2>(k, s_keys);
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t j = threadIdx.x * (uint32_t)E + r;
+    if (j < count) {
+      list[j] = (uint32_t)__double2loint(k[r]);
+      if (keys) keys[j] = ((uint64_t)seg << 32) | (uint32_t)__double2hiint(k[r]);
+    }
+  }
+}
+
+// Sorts each tile's list by (depth, id) and writes its range (0, 0 for an
+// empty one).  One workgroup of T threads per tile, lists of at most 16 T.
+template <int T>
+__global__ __launch_bounds__(T) void k_tile_sort(int V, int ld,
+                                                 const uint32_t* __restrict__ starts,
+                                                 const uint32_t* __restrict__ seg_base,
+                                                 const uint32_t* __restrict__ depth_bits,
+                                                 uint32_t* __restrict__ vals,
+                                                 uint32_t* __restrict__ ranges,
+                                                 uint64_t* __restrict__ keys) {
+  __shared__ double s_keys[T > 64 ? 16 * T : 1];
+  const uint32_t seg = blockIdx.x;
+  const uint32_t start = starts[seg], end = starts[seg + 1];
+  const uint32_t count = end - start;
+  if (threadIdx.x == 0) {
+    ranges[2 * (size_t)seg] = count > 0 ? start : 0u;
+    ranges[2 * (size_t)seg + 1] = count > 0 ? end : 0u;
+  }
+  if (count == 0) return;
+  int lo = 0, hi = V - 1;  // last view whose base <= seg
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (seg_base[mid] <= seg) lo = mid; else hi = mid - 1;
+  }
+  const uint32_t* depth = depth_bits + (size_t)lo * ld;
+  uint32_t* list = vals + start;
+  uint64_t* lk = keys ? keys + start : nullptr;
+  if (count <= T)
+    sort_list<1, T>(list, count, depth, lk, seg, s_keys);
+  else if (count <= 2 * T)
+    sort_list<2, T>(list, count, depth, lk, seg, s_keys);
+  else if (count <= 4 * T)
+    sort_list<4, T>(list, count, depth, lk, seg, s_keys);
+  else if (count <= 8 * T)
+    sort_list<8, T>(list, count, depth, lk, seg, s_keys);
+  else
+    sort_list<16, T>(list, count, depth, lk, seg, s_keys);
 }
 
 // Segment boundaries of the sorted segment ids, four per thread (one 16-B
@@ -1055,16 +1502,37 @@ size_t bin_sort_workspace_bytes(int V, int ld, int64_t cap, int64_t nseg) {
   return make_layout(V, ld, cap, nseg).bytes;
 }
 
+namespace {
+// The direct route's buffers, in the space of the radix sorts' keys, values
+// and instances, which it leaves free: the tile counts (n_segments + 1) and
+// the rows of counts, one per chunk of a view.
+struct DirectPlan {
+  bool possible;
+  size_t counts, rows;
+};
+// Most (view, Gaussian) pairs of the direct route.  All of gs_bin_sort but its
+// wait for the host, radix sorts -> direct, in us: 10 k pairs (16 k instances)
+// 134 -> 50, 180 k (0.41 M) 190 -> 57, 300 k (1.1 M) 185 -> 78, 480 k (1.3 M)
+// 204 -> 79, 1.2 M (6.4 M) 283 -> 204, 1.8 M (9.6 M) 327 -> 271, 3 M (16 M)
+// 425 -> 428, 6 M (32 M) 704 -> 851: its lists are written word by word, the
+// radix passes write runs.
+constexpr int64_t kDirectPairs = 3000000;
+constexpr uint32_t kDirectLongest = 4096;  // keys a sorting workgroup holds
+
+DirectPlan plan_direct(const BinSortPlan& p, const Layout& L) {
+  DirectPlan d{};
+  const int64_t chunks = cdiv((uint64_t)p.n, kCountChunk);
+  d.counts = L.dk0;
+  d.rows = d.counts + align_up(((size_t)p.n_segments + 1) * 4);
+  d.possible = (int64_t)p.n_views * p.n <= kDirectPairs && p.max_tiles <= kChunkTiles &&
+               d.rows + (size_t)chunks * (size_t)p.n_segments * 4 <= L.pcount;
+  return d;
+}
+}  // namespace
+
 hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
-                           const gs_camera* cams_dev, void* ws, hipStream_t s,
-                           uint32_t** d_stats) {
+                           const gs_camera* cams_dev, void* ws, uint32_t* stats, hipStream_t s) {
   const Layout L = make_layout(p.n_views, p.ld, p.capacity, p.n_segments);
-  const uint32_t N = (uint32_t)p.n_views * (uint32_t)p.n;
-  uint32_t* stats = at<uint32_t>(ws, L.stats);
-  *d_stats = stats;
-  hipLaunchKernelGGL(k_view_info, dim3(1), dim3(kBlock), 0, s, cams_dev, p.n_views,
-                     at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), stats);
-  if (N == 0) return hipGetLastError();
   StageScope scope(kStDepthSort, s);
   // chunks of kCountChunk Gaussians per view; views on grid rows (beyond
   // 65535 they loop)
@@ -1081,7 +1549,21 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
   // number), and where each chunk's instances start in emission order,
   // which keeps the views in order (only read once the host has checked
   // that the total fits 32 bits)
-  hipLaunchKernelGGL(k_stage1_close, dim3(3), dim3(kBlock), 0, s, part, vis, icnt, nchunk, stats);
+  hipLaunchKernelGGL(k_stage1_close, dim3(4), dim3(kBlock), 0, s, part, vis, icnt, nchunk, stats,
+                     cams_dev, p.n_views, at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv));
+  const DirectPlan d = plan_direct(p, L);
+  if (d.possible) {
+    // the tile counts do not wait for the host
+    uint32_t* counts = at<uint32_t>(ws, d.counts);
+    uint32_t* rows = at<uint32_t>(ws, d.rows);
+    const uint32_t nseg = (uint32_t)p.n_segments;
+    hipLaunchKernelGGL(k_tile_count, dim3(gx, gy), dim3(kChunkThreads), 0, s, p.n, p.ld,
+                       p.n_views, proj.tiles_touched, reinterpret_cast<uint32_t*>(proj.splat),
+                       at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), rows);
+    hipLaunchKernelGGL(k_tile_columns, dim3(cdiv(nseg, 64u)), dim3(1024), 0, s, p.n_views, nseg,
+                       gx, at<uint32_t>(ws, L.seg_base), rows, counts);
+    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nseg, stats + 6);
+  }
   return hipGetLastError();
 }
 
@@ -1147,13 +1629,33 @@ void depth_count_emit(const BinSortPlan& p, const gs_projected& proj, const Layo
 }
 }  // namespace
 
-hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj,
-                           const gs_camera* cams_dev, uint32_t M, uint32_t dmin, uint32_t dmax,
-                           uint32_t N, gs_tile_lists& lists, void* ws, hipStream_t s) {
-  (void)cams_dev;
+hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const uint32_t* stats,
+                           gs_tile_lists& lists, void* ws, hipStream_t s) {
+  const uint32_t dmin = stats[0], dmax = stats[1], M = stats[2], N = stats[4];
   const Layout L = make_layout(p.n_views, p.ld, p.capacity, p.n_segments);
   if (M == 0) {
     launch_fill_u32(lists.ranges, 0u, 2 * p.n_segments, s);
+    return hipGetLastError();
+  }
+  const DirectPlan d = plan_direct(p, L);
+  if (d.possible && stats[6] <= kDirectLongest) {
+    const uint32_t* starts = at<uint32_t>(ws, d.counts);
+    {
+      StageScope scope(kStEmit, s);
+      const dim3 grid(cdiv((uint64_t)p.n, kCountChunk),
+                      std::min<uint32_t>((uint32_t)p.n_views, 65535u));
+      hipLaunchKernelGGL(k_tile_fill, grid, dim3(kChunkThreads), 0, s, p.n, p.ld, p.n_views,
+                         proj.tiles_touched, at<uint32_t>(ws, L.iparts),
+                         reinterpret_cast<uint32_t*>(proj.splat), at<uint32_t>(ws, L.seg_base),
+                         at<int32_t>(ws, L.txv), at<uint32_t>(ws, d.rows), starts, lists.vals,
+                         lists.gv_base);
+    }
+    StageScope scope(kStSegmentSort, s);
+    const bool wide = stats[6] > 1024;
+    hipLaunchKernelGGL(wide ? k_tile_sort<256> : k_tile_sort<64>, dim3((unsigned)p.n_segments),
+                       dim3(wide ? 256 : 64), 0, s, p.n_views, p.ld, starts,
+                       at<uint32_t>(ws, L.seg_base), proj.depth_bits, lists.vals, lists.ranges,
+                       lists.keys);
     return hipGetLastError();
   }
   // the tile sort runs inside each view on the bits of its tile index (at
