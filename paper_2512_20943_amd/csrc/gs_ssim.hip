@@ -3,7 +3,7 @@
 // C1 = 0.01^2, C2 = 0.03^2, averaged over every image value.
 //
 // Two streaming passes.  A workgroup owns a strip of kSW output columns (one
-// per thread) and a band of kBand output rows; it walks the band's input
+// per thread) and a band of up to kBand output rows; it walks the band's input
 // rows top to bottom, staging each row of the strip plus its kR-column
 // margins in LDS (two row buffers, the next row's loads in flight while the
 // current one is summed), takes each thread's horizontal 11-tap sums, and
@@ -28,7 +28,7 @@ namespace {
 constexpr int kR = 5;               // window radius
 constexpr int kTaps = 2 * kR + 1;
 constexpr int kSW = 128;            // strip width: output columns, one per thread
-constexpr int kBand = 64;           // output rows per workgroup
+constexpr int kBand = 64;           // most output rows per workgroup
 constexpr int kSI = kSW + 2 * kR;   // staged columns of one input row
 constexpr float kC1 = 0.01f * 0.01f, kC2 = 0.03f * 0.03f;
 
@@ -79,11 +79,11 @@ __device__ __forceinline__ void store_row(float (*buf)[kSI], const RowRegs<NP>& 
 // next row's loads are in flight while a row is summed; the ring slot of
 // row i is i mod 11, and the rows are unrolled by 11 so that every slot
 // index is static.
-template <int NP, int NS, typename Horiz, typename Out, typename Centre, typename Ahead>
+template <int BAND, int NP, int NS, typename Horiz, typename Out, typename Centre, typename Ahead>
 __device__ __forceinline__ void walk_band(const float* const* src, int W, int H, int x0, int y0,
                                           const Window& win, float (*buf)[NP][kSI], Horiz horiz,
                                           Out out, Centre centre, Ahead ahead) {
-  const int rows = min(kBand, H - y0) + 2 * kR;  // same for the whole workgroup
+  const int rows = min(BAND, H - y0) + 2 * kR;  // same for the whole workgroup
   float ring[kTaps][NS];
   RowRegs<NP> nx;
   load_row<NP>(nx, src, W, H, x0, y0 - kR);
@@ -120,6 +120,7 @@ __device__ __forceinline__ void walk_band(const float* const* src, int W, int H,
   }
 }
 
+template <int BAND>
 __global__ __launch_bounds__(kSW) void k_ssim_stats(const float* __restrict__ img,
                                                    const float* __restrict__ tgt, int W, int H,
                                                    Window win, float lambda, float inv_count,
@@ -129,13 +130,13 @@ __global__ __launch_bounds__(kSW) void k_ssim_stats(const float* __restrict__ im
   __shared__ double red[kSW / 64];
   const size_t plane = (size_t)W * H;
   const int pl = blockIdx.z, t = threadIdx.x;
-  const int x0 = blockIdx.x * kSW, y0 = blockIdx.y * kBand;
+  const int x0 = blockIdx.x * kSW, y0 = blockIdx.y * BAND;
   const int x = x0 + t;
   const float* srcs[2] = {img + pl * plane, tgt + pl * plane};
   float* a = amaps + (size_t)pl * 3 * plane;
   double part = 0.0;
-  const int rows = min(kBand, H - y0) + 2 * kR;
-  walk_band<2, 5>(
+  const int rows = min(BAND, H - y0) + 2 * kR;
+  walk_band<BAND, 2, 5>(
       srcs, W, H, x0, y0, win, buf,
       [&](const float (*in)[kSI], float* hs) {
 #pragma unroll
@@ -215,6 +216,7 @@ __global__ __launch_bounds__(1024) void k_sum_partials(const double* __restrict_
   }
 }
 
+template <int BAND>
 __global__ __launch_bounds__(kSW) void k_ssim_grad(const float* __restrict__ img,
                                                   const float* __restrict__ tgt, int W, int H,
                                                   Window win, float lambda, float inv_count,
@@ -223,15 +225,15 @@ __global__ __launch_bounds__(kSW) void k_ssim_grad(const float* __restrict__ img
   __shared__ float buf[2][3][kSI];
   const size_t plane = (size_t)W * H;
   const int pl = blockIdx.z, t = threadIdx.x;
-  const int x0 = blockIdx.x * kSW, y0 = blockIdx.y * kBand;
+  const int x0 = blockIdx.x * kSW, y0 = blockIdx.y * BAND;
   const int x = x0 + t;
   const float* a = amaps + (size_t)pl * 3 * plane;
   const float* srcs[3] = {a, a + plane, a + 2 * plane};
-  const int rows = min(kBand, H - y0) + 2 * kR;
+  const int rows = min(BAND, H - y0) + 2 * kR;
   // x and y at this thread's pixel of the next output row, loaded a row
   // ahead of their use
   float xa = 0.f, ya = 0.f, xc = 0.f, yc = 0.f;
-  walk_band<3, 3>(
+  walk_band<BAND, 3, 3>(
       srcs, W, H, x0, y0, win, buf,
       [&](const float (*in)[kSI], float* hs) {
 #pragma unroll
@@ -294,17 +296,51 @@ void launch_l1_dssim(const float* image, const float* target, int planes, int H,
   const Window win = make_window();
   const double count = (double)planes * (double)H * (double)W;
   const float inv = (float)(1.0 / count);
-  const dim3 grid((W + kSW - 1) / kSW, (H + kBand - 1) / kBand, planes);
   float* amaps = static_cast<float*>(ws);
   double* partial =
       reinterpret_cast<double*>(static_cast<char*>(ws) + (size_t)planes * 3 * H * W * sizeof(float));
+  const int strips = (W + kSW - 1) / kSW;
+  auto groups = [&](int rows) { return (size_t)strips * ((H + rows - 1) / rows) * planes; };
+  // Shorter bands where kBand rows would leave the chip nearly empty and the
+  // pair would wait for one band's 74 serial rows; each band reads 2 kR more
+  // rows than it yields, which costs more once the chip is full.  Both
+  // kernels, bands of 64 / 32 / 16 / 8 rows, in us: one 128x128 view (6
+  // workgroups of 64 rows) 108 / 64 / 41 / 30, 900x700 (264) - / - / 61 / 55,
+  // 1352x1014 (528) 140 / 95 / 82 / 94, 1920x1080 (765) 142 / 107 / 113 / 122,
+  // 3 views of 1352x1014 (1,584) 198 / 170 / 190 / 225, 4 views (2,112) 243 /
+  // 246 / 262 / 313.
+  const size_t full = groups(kBand);
+  int band = full <= 300 ? 8 : full <= 650 ? 16 : full <= 1600 ? 32 : kBand;
+  // the workspace holds one loss partial per workgroup of kBand rows; those
+  // of shorter bands lie in grad, which is written after they are summed
+  // (not where it is misaligned for them, too small, or one of the images,
+  // which the adjoint still reads)
+  const size_t values = (size_t)planes * H * W;
+  auto apart = [&](const float* p) { return p + values <= grad || grad + values <= p; };
+  if (reinterpret_cast<uintptr_t>(grad) % sizeof(double) != 0 ||
+      groups(band) * sizeof(double) > values * sizeof(float) || !apart(image) || !apart(target))
+    band = kBand;
+  if (band < kBand) partial = reinterpret_cast<double*>(grad);
+  const dim3 grid(strips, (H + band - 1) / band, planes);
+  auto stats = k_ssim_stats<kBand>;
+  auto adjoint = k_ssim_grad<kBand>;
+  if (band == 32) {
+    stats = k_ssim_stats<32>;
+    adjoint = k_ssim_grad<32>;
+  } else if (band == 16) {
+    stats = k_ssim_stats<16>;
+    adjoint = k_ssim_grad<16>;
+  } else if (band == 8) {
+    stats = k_ssim_stats<8>;
+    adjoint = k_ssim_grad<8>;
+  }
   StageScope scope(kStDssim, s);
-  hipLaunchKernelGGL(k_ssim_stats, grid, dim3(kSW), 0, s, image, target, W, H, win, lambda, inv,
-                     amaps, partial);
+  hipLaunchKernelGGL(stats, grid, dim3(kSW), 0, s, image, target, W, H, win, lambda, inv, amaps,
+                     partial);
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, s, (const double*)partial,
-                     tiles_of(planes, H, W), lambda, loss);
-  hipLaunchKernelGGL(k_ssim_grad, grid, dim3(kSW), 0, s, image, target, W, H, win, lambda, inv,
-                     amaps, grad);
+                     groups(band), lambda, loss);
+  hipLaunchKernelGGL(adjoint, grid, dim3(kSW), 0, s, image, target, W, H, win, lambda, inv, amaps,
+                     grad);
 }
 
 }  // namespace gs
