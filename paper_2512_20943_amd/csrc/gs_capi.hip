@@ -555,10 +555,12 @@ size_t gs_render_batched_workspace_size(int V) {
   return gs::render_batched_workspace_bytes(V);
 }
 
-gs_status gs_render_fwd_batched(gs_ctx* c, const gs_projected* proj, const gs_tile_lists* lists,
-                                const gs_camera* ch, const gs_camera* cd, int V,
-                                const gs_opts* opts, float* images, void* ws, size_t ws_bytes,
-                                void* stream) {
+}  // extern "C"
+
+gs_status gs::render_fwd_batched(gs_ctx* c, const gs_projected* proj, const gs_tile_lists* lists,
+                                 const gs_camera* ch, const gs_camera* cd, int V,
+                                 const gs_opts* opts, float* images, float* const* outs, void* ws,
+                                 size_t ws_bytes, void* stream) {
   if (!c) return fail(nullptr, GS_ERR_INVALID_ARG, "ctx is NULL");
   TimerGuard timer_guard(c);
   GS_TRY(check_cams(c, ch, cd, V));
@@ -569,17 +571,27 @@ gs_status gs_render_fwd_batched(gs_ctx* c, const gs_projected* proj, const gs_ti
   const int64_t nseg = segments_of(ch, V);
   if (lists->n_segments != nseg)
     return fail(c, GS_ERR_INVALID_ARG, "tile lists were built for other cameras");
-  if (!images) return fail(c, GS_ERR_INVALID_ARG, "images is NULL");
+  if (!images && !outs) return fail(c, GS_ERR_INVALID_ARG, "images is NULL");
   const size_t need = gs::render_batched_workspace_bytes(V);
   if (!ws || ws_bytes < need)
     return fail(c, GS_ERR_OOM, "batched render workspace %zu < %zu bytes", ws_bytes, need);
   GS_TRY(check_ws_align(c, ws));
   GS_TRY(use_device(c));
   const float zero[3] = {0.f, 0.f, 0.f};
-  gs::launch_render_batched(*proj, *lists, cd, V, nseg, opts ? opts->bg : zero, images, ws,
+  gs::launch_render_batched(*proj, *lists, cd, V, nseg, opts ? opts->bg : zero, images, outs, ws,
                             (hipStream_t)stream);
   GS_LAUNCHED(c, "render_fwd_batched");
   return GS_OK;
+}
+
+extern "C" {
+
+gs_status gs_render_fwd_batched(gs_ctx* c, const gs_projected* proj, const gs_tile_lists* lists,
+                                const gs_camera* ch, const gs_camera* cd, int V,
+                                const gs_opts* opts, float* images, void* ws, size_t ws_bytes,
+                                void* stream) {
+  return gs::render_fwd_batched(c, proj, lists, ch, cd, V, opts, images, nullptr, ws, ws_bytes,
+                                stream);
 }
 
 gs_status gs_render_bwd(gs_ctx* c, const gs_gaussians* frame, const gs_projected* proj,

@@ -118,7 +118,14 @@ void launch_render_fwd_l1(const gs_projected& proj, const gs_tile_lists& lists, 
 size_t render_batched_workspace_bytes(int V);
 void launch_render_batched(const gs_projected& proj, const gs_tile_lists& lists,
                            const gs_camera* cams_dev, int V, int64_t total_segments,
-                           const float bg[3], float* images, void* ws, hipStream_t s);
+                           const float bg[3], float* images, float* const* outs, void* ws,
+                           hipStream_t s);
+// gs_render_fwd_batched, request v's planes at outs[v] (device table of V
+// device pointers) instead of packed in images when outs is not null.
+gs_status render_fwd_batched(gs_ctx* c, const gs_projected* proj, const gs_tile_lists* lists,
+                             const gs_camera* cams_host, const gs_camera* cams_dev, int V,
+                             const gs_opts* opts, float* images, float* const* outs, void* ws,
+                             size_t ws_bytes, void* stream);
 void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
                        const float bg[3], const float* final_T, const int32_t* n_contrib,
                        const float* dL_dimage, float* rows, float* grad2d, hipStream_t s);

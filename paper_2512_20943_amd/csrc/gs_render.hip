@@ -841,7 +841,7 @@ __global__ __launch_bounds__(QUADS ? 256 : 64) void k_render_batched(
     const float4* __restrict__ splat, int ld, const uint32_t* __restrict__ vals,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ seg_base,
     const int64_t* __restrict__ pix_base, const int2* __restrict__ wh, int V, uint32_t seg0,
-    float bg0, float bg1, float bg2, float* __restrict__ images) {
+    float bg0, float bg1, float bg2, float* __restrict__ images, float* const* __restrict__ outs) {
   const uint32_t item = seg0 + blockIdx.x;
   int lo = 0, hi = V - 1;  // request: last v with seg_base[v] <= item
   while (lo < hi) {
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(QUADS ? 256 : 64) void k_render_batched(
   const int tile = (int)(item - seg_base[lo]);
   const int ty = tile / TX, tx = tile - ty * TX;
   const float4* sv = splat + kSplatF4 * (size_t)lo * ld;
-  float* image = images + 3 * pix_base[lo];
+  float* image = outs ? outs[lo] : images + 3 * pix_base[lo];
   if constexpr (QUADS) {
     __shared__ QuadStage sh[4];
     render_tile_quads<false>(sh, sv, vals, ranges[item], tx, ty, d.x, d.y, bg0, bg1, bg2, image,
@@ -1535,7 +1535,8 @@ size_t render_batched_workspace_bytes(int V) {
 
 void launch_render_batched(const gs_projected& proj, const gs_tile_lists& lists,
                            const gs_camera* cams_dev, int V, int64_t total_segments,
-                           const float bg[3], float* images, void* ws, hipStream_t s) {
+                           const float bg[3], float* images, float* const* outs, void* ws,
+                           hipStream_t s) {
   char* w = static_cast<char*>(ws);
   uint32_t* seg_base = reinterpret_cast<uint32_t*>(w);
   w += 256 * ((((size_t)V + 1) * 4 + 255) / 256);
@@ -1552,7 +1553,8 @@ void launch_render_batched(const gs_projected& proj, const gs_tile_lists& lists,
                        dim3((unsigned)std::min(kMost, total_segments - s0)),
                        dim3(quads ? 256 : 64), 0, s, reinterpret_cast<const float4*>(proj.splat),
                        proj.ld, lists.vals, reinterpret_cast<const uint2*>(lists.ranges),
-                       seg_base, pix_base, wh, V, (uint32_t)s0, bg[0], bg[1], bg[2], images);
+                       seg_base, pix_base, wh, V, (uint32_t)s0, bg[0], bg[1], bg[2], images,
+                       outs);
 }
 
 void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
