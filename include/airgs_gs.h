@@ -545,6 +545,16 @@ gs_status gs_keyframe_temporal_l1(gs_ctx* ctx, const float* x, const float* x_pr
                                   int bound, int64_t ld, float weight, float* grad,
                                   double* loss_dev, void* stream);
 
+/* Keep-masks of usage pruning (Sec. III-C): WRITES levels masks of gh x gw
+ * bytes; mask l is 0 for the drops[l] least used of the n Gaussians (equal
+ * usage: lower id dropped first) and for padding texels, else 1.  usage:
+ * gs_opts.usage counts; drops: host array, each in [0, n].  workspace:
+ * gs_usage_masks_workspace_size(n) bytes. */
+size_t gs_usage_masks_workspace_size(int n);
+gs_status gs_usage_masks(gs_ctx* ctx, const uint32_t* usage, int n, int gw, int gh,
+                         const int32_t* drops, int levels, uint8_t* masks, void* workspace,
+                         size_t ws_bytes, void* stream);
+
 /* Low-opacity culling (Sec. III-B: Gaussians whose opacity falls below a
  * threshold are discarded during keyframe training).  Gaussian i < n is kept
  * iff sigmoid(opacity_logit[i]) >= min_opacity, decided as logit >=

@@ -739,6 +739,33 @@ gs_status gs_keyframe_temporal_l1(gs_ctx* c, const float* x, const float* x_prev
   return GS_OK;
 }
 
+size_t gs_usage_masks_workspace_size(int n) {
+  return n < 0 ? 0 : gs::usage_masks_workspace_bytes(n);
+}
+
+gs_status gs_usage_masks(gs_ctx* c, const uint32_t* usage, int n, int gw, int gh,
+                         const int32_t* drops, int levels, uint8_t* masks, void* ws,
+                         size_t ws_bytes, void* stream) {
+  if (!c) return fail(nullptr, GS_ERR_INVALID_ARG, "ctx is NULL");
+  TimerGuard timer_guard(c);
+  if (n < 0 || gw < 0 || gh < 0 || (int64_t)gw * gh < n || levels < 0)
+    return fail(c, GS_ERR_INVALID_ARG, "bad n, grid or level count");
+  if ((n > 0 && !usage) || (levels > 0 && (!drops || !masks)))
+    return fail(c, GS_ERR_INVALID_ARG, "NULL buffer");
+  for (int l = 0; l < levels; ++l)
+    if (drops[l] < 0 || drops[l] > n)
+      return fail(c, GS_ERR_INVALID_ARG, "level %d drops %d of %d", l, drops[l], n);
+  const size_t need = gs::usage_masks_workspace_bytes(n);
+  if (!ws || ws_bytes < need)
+    return fail(c, GS_ERR_OOM, "usage mask workspace %zu < %zu bytes", ws_bytes, need);
+  GS_TRY(check_ws_align(c, ws));
+  GS_TRY(use_device(c));
+  const hipError_t e = gs::launch_usage_masks(usage, n, (size_t)gw * (size_t)gh, drops, levels,
+                                              masks, ws, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_fail(c, e, "usage masks");
+  return GS_OK;
+}
+
 size_t gs_cull_workspace_size(int n) { return n < 0 ? 0 : gs::keep_workspace_bytes(n); }
 
 gs_status gs_cull_low_opacity(gs_ctx* c, const float* logit, int n, float min_opacity,

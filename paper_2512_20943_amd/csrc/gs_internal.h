@@ -106,6 +106,9 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
                            const gs_camera* cams_dev, void* ws, uint32_t* stats, hipStream_t s);
 hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const uint32_t* stats,
                            gs_tile_lists& lists, void* ws, hipStream_t s);
+size_t usage_masks_workspace_bytes(int n);
+hipError_t launch_usage_masks(const uint32_t* usage, int n, size_t texels, const int32_t* drops,
+                              int levels, uint8_t* masks, void* ws, hipStream_t s);
 // render
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int n_views, int W,
                        int H, const float bg[3], float* image, float* final_T,

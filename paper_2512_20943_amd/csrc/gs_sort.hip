@@ -1327,6 +1327,44 @@ inline int bits_for(uint64_t count) {  // bits to hold values 0 .. count-1
   return b;
 }
 
+// ---------------------------------------------------- usage keep-masks
+// Ids beside the usage counts to be sorted (the sort overwrites its input).
+__global__ __launch_bounds__(kBlock) void k_usage_pairs(const uint32_t* __restrict__ usage,
+                                                        uint32_t n, uint32_t* __restrict__ key,
+                                                        uint32_t* __restrict__ id) {
+  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  key[i] = usage[i];
+  id[i] = i;
+}
+
+// rank[id] = position of id in the ordering.
+__global__ __launch_bounds__(kBlock) void k_usage_rank(const uint32_t* __restrict__ order,
+                                                       uint32_t n, uint32_t* __restrict__ rank) {
+  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) rank[order[i]] = i;
+}
+
+constexpr int kMaskLevels = 64;
+struct MaskDrops {
+  uint32_t d[kMaskLevels];
+};
+
+// masks[level][texel] = 1 where the texel's Gaussian ranks at or above the
+// level's drop count, 0 below it and in the padding.  The ranks are read once
+// for all levels of a launch, and the masks come out as whole lines: written
+// straight from the ordering they would be scattered bytes.
+__global__ __launch_bounds__(kBlock) void k_usage_masks(const uint32_t* __restrict__ rank,
+                                                        uint32_t n, size_t texels, int levels,
+                                                        MaskDrops drops,
+                                                        uint8_t* __restrict__ masks) {
+  const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t >= texels) return;
+  const bool real = t < n;
+  const uint32_t r = real ? rank[t] : 0u;
+  for (int l = 0; l < levels; ++l) masks[(size_t)l * texels + t] = real && r >= drops.d[l];
+}
+
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Fewest passes with digits of 8 or 9 bits (wider digits cost more per pass
@@ -1496,6 +1534,57 @@ void launch_fill_f32(float* p, float value, int64_t count, hipStream_t s) {
   const int blocks = (int)std::min<int64_t>(want, 4096);
   StageScope scope(kStFill, s);
   hipLaunchKernelGGL(k_fill_f32, dim3(blocks), dim3(256), 0, s, p, value, (size_t)count);
+}
+
+// Workspace of the keep-masks: two (usage, id) buffer pairs, the digit counts
+// of one pass and the ranks, which take the place of the pair the sort leaves.
+static Layout usage_layout(int n) {
+  Layout L{};
+  size_t o = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = o;
+    o = align_up(o + bytes);
+    return at;
+  };
+  L.dk0 = take((size_t)n * 4);
+  L.dk1 = take((size_t)n * 4);
+  L.dv0 = take((size_t)n * 4);
+  L.dv1 = take((size_t)n * 4);
+  L.pcount = take((size_t)512 * std::max<size_t>(cdiv((uint64_t)n, kPart), 1) * 4);
+  L.dtotal = take(512 * 4);
+  L.bytes = o;
+  return L;
+}
+
+size_t usage_masks_workspace_bytes(int n) { return usage_layout(n).bytes; }
+
+hipError_t launch_usage_masks(const uint32_t* usage, int n, size_t texels, const int32_t* drops,
+                              int levels, uint8_t* masks, void* ws, hipStream_t s) {
+  if (levels == 0 || texels == 0) return hipSuccess;
+  const Layout L = usage_layout(n);
+  StageScope scope(kStCompact, s);
+  uint32_t* k0 = at<uint32_t>(ws, L.dk0);
+  uint32_t* v0 = at<uint32_t>(ws, L.dv0);
+  uint32_t* v1 = at<uint32_t>(ws, L.dv1);
+  const uint32_t blocks = cdiv((uint64_t)n, kBlock);
+  if (n > 0) {
+    hipLaunchKernelGGL(k_usage_pairs, dim3(blocks), dim3(kBlock), 0, s, usage, (uint32_t)n, k0,
+                       v0);
+    // equal usage keeps the order of the ids: the sort is stable
+    const int which =
+        radix_sort<uint32_t>(k0, at<uint32_t>(ws, L.dk1), v0, v1, (uint32_t)n, 32,
+                             ViewStarts{nullptr, 0, 1}, SortSpec{0, nullptr, nullptr}, ws, L, s);
+    hipLaunchKernelGGL(k_usage_rank, dim3(blocks), dim3(kBlock), 0, s, which ? v1 : v0,
+                       (uint32_t)n, k0);
+  }
+  for (int l = 0; l < levels; l += kMaskLevels) {
+    MaskDrops d{};
+    const int count = std::min(kMaskLevels, levels - l);
+    for (int k = 0; k < count; ++k) d.d[k] = (uint32_t)drops[l + k];
+    hipLaunchKernelGGL(k_usage_masks, dim3(cdiv(texels, kBlock)), dim3(kBlock), 0, s, k0,
+                       (uint32_t)n, texels, count, d, masks + (size_t)l * texels);
+  }
+  return hipGetLastError();
 }
 
 size_t bin_sort_workspace_bytes(int V, int ld, int64_t cap, int64_t nseg) {

@@ -157,6 +157,12 @@ def load() -> ctypes.CDLL:
     lib.gs_cull_workspace_size.restype = ctypes.c_size_t
     lib.gs_cull_low_opacity.argtypes = [c_void_p, c_void_p, ctypes.c_int, c_float, c_void_p,
                                         P(c_int32), c_void_p, ctypes.c_size_t, c_void_p]
+    lib.gs_usage_masks_workspace_size.argtypes = [ctypes.c_int]
+    lib.gs_usage_masks_workspace_size.restype = ctypes.c_size_t
+    lib.gs_usage_masks.argtypes = [c_void_p, c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                   P(c_int32), ctypes.c_int, c_void_p, c_void_p, ctypes.c_size_t,
+                                   c_void_p]
+    lib.gs_usage_masks.restype = c_int32
     lib.gs_gather_planes.argtypes = [c_void_p, c_void_p, c_int64, ctypes.c_int, c_void_p,
                                      ctypes.c_int, c_void_p, c_int64, c_void_p]
     lib.gs_residual_delta.argtypes = [c_void_p, c_void_p, c_void_p, c_void_p, ctypes.c_int,
@@ -227,6 +233,7 @@ def exported_symbols():
             "gs_collect_timing", "gs_stage_name", "gs_render_batched_workspace_size",
             "gs_render_fwd_batched", "gs_sq_error", "gs_l1_dssim_workspace_size",
             "gs_l1_dssim_loss_grad", "gs_keyframe_temporal_l1", "gs_cull_workspace_size",
+            "gs_usage_masks_workspace_size", "gs_usage_masks",
             "gs_cull_low_opacity", "gs_gather_planes", "gs_residual_delta",
             "gs_quantize_delta", "gs_apply_quantized_update", "gs_render_fwd_l1_workspace_size",
             "gs_render_fwd_l1", "gs_render_fwd_l1_noalloc", "gs_set_work_counters",
@@ -631,6 +638,17 @@ def gs_keyframe_temporal_l1(ctx: Context, x, x_prev, bound: int, weight: float, 
     ctx.check(ctx.lib.gs_keyframe_temporal_l1(ctx.handle, _ptr(x), _ptr(x_prev), rows, bound, ld,
                                               float(weight), _ptr(grad), _ptr(loss_dev),
                                               _stream(stream)))
+
+
+def gs_usage_masks(ctx: Context, usage, n: int, gw: int, gh: int, drops, masks, stream=None):
+    """masks (len(drops), gh, gw) uint8: mask l is 0 for the drops[l] least
+    used of the n Gaussians (equal usage: lower id first) and for padding."""
+    levels = len(drops)
+    size = int(ctx.lib.gs_usage_masks_workspace_size(n))
+    ws = torch.empty(max(size, 1), dtype=torch.uint8, device=usage.device)
+    ctx.check(ctx.lib.gs_usage_masks(ctx.handle, _ptr(usage), n, gw, gh,
+                                     (c_int32 * levels)(*drops), levels, _ptr(masks), _ptr(ws),
+                                     ws.numel(), _stream(stream)))
 
 
 def gs_cull_low_opacity(ctx: Context, opacity_logit, n: int, min_opacity: float, kept_index,
