@@ -784,12 +784,12 @@ gs_status gs_cull_low_opacity(gs_ctx* c, const float* logit, int n, float min_op
   GS_TRY(check_ws_align(c, ws));
   GS_TRY(use_device(c));
   hipStream_t s = (hipStream_t)stream;
-  const uint32_t* d_total = gs::launch_keep_low_opacity(
-      logit, n, gs::opacity_logit_threshold(min_opacity), kept_index, ws, s);
+  // the last kernel writes the count into the context's pinned slot
+  *c->pinned = 0;
+  gs::launch_keep_low_opacity(logit, n, gs::opacity_logit_threshold(min_opacity), kept_index, ws,
+                              c->pinned, s);
   GS_LAUNCHED(c, "cull_low_opacity");
-  hipError_t e = hipMemcpyAsync(c->pinned, d_total, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
-  if (e != hipSuccess) return hip_fail(c, e, "kept count readback");
-  e = hipStreamSynchronize(s);
+  const hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
   *kept_host = (int32_t)*c->pinned;
   return GS_OK;

@@ -3,10 +3,13 @@
 // training) as an order-preserving stream compaction, and the gather that
 // applies the resulting index list to parameter or optimizer-state planes.
 //
-// Compaction in three launches over chunks of 1024 Gaussians: count the kept
-// ones per chunk, scan the chunk counts in one workgroup, then rank inside
-// each chunk with wave ballots and write the kept indices in their original
-// order.  HBM-bound: 4 B read twice and at most 4 B written per Gaussian.
+// Compaction over chunks of 1024 Gaussians: count the kept ones per chunk,
+// then rank inside each chunk with wave ballots and write the kept indices in
+// their original order.  Up to kSumChunks chunks every workgroup of the
+// second launch adds up the counts before its own; beyond, a launch in
+// between scans them.  4 B are read twice and at most 4 B written per
+// Gaussian, so at ordinary sizes the launches are what it costs.
+#include <algorithm>
 #include <cmath>
 
 #include "gs_internal.h"
@@ -33,8 +36,7 @@ __global__ __launch_bounds__(256) void k_keep_count(const float* __restrict__ lo
   if (threadIdx.x == 0) counts[blockIdx.x] = (uint32_t)(s[0] + s[1] + s[2] + s[3]);
 }
 
-// Exclusive scan of nb chunk counts in one workgroup of 1024 threads; the
-// total goes to counts[nb].
+// Exclusive scan of nb chunk counts in one workgroup of 1024 threads.
 __global__ __launch_bounds__(1024) void k_keep_scan(uint32_t* __restrict__ counts, int nb) {
   __shared__ uint32_t s_wave[16];
   __shared__ uint32_t s_carry;
@@ -58,14 +60,18 @@ __global__ __launch_bounds__(1024) void k_keep_scan(uint32_t* __restrict__ count
     if (threadIdx.x == 1023) s_carry = before + x;
     __syncthreads();
   }
-  if (threadIdx.x == 0) counts[nb] = s_carry;
 }
 
+// SUM: offsets holds the chunk counts, else their scan.  The last workgroup
+// stores the number kept.
+template <bool SUM>
 __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ logit, int n,
                                                     double thr,
                                                     const uint32_t* __restrict__ offsets,
-                                                    int32_t* __restrict__ index) {
+                                                    int32_t* __restrict__ index,
+                                                    uint32_t* __restrict__ total) {
   __shared__ uint32_t s_cnt[16];
+  __shared__ uint32_t s_sum[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int base = blockIdx.x * kChunk;
   // pass k covers Gaussians base + k*256 + [0, 256): 4 waves of 64, so the
@@ -78,9 +84,15 @@ __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ lo
     const uint64_t b = __ballot(f[k]);
     if (lane == 0) s_cnt[k * 4 + wave] = (uint32_t)__popcll(b);
   }
+  if constexpr (SUM) {
+    uint32_t x = 0;
+    for (uint32_t c = threadIdx.x; c < blockIdx.x; c += 256) x += offsets[c];
+    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+    if (lane == 0) s_sum[wave] = x;
+  }
   __syncthreads();
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  uint32_t run = offsets[blockIdx.x];
+  uint32_t run = SUM ? (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) : offsets[blockIdx.x];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uint64_t b = __ballot(f[k]);
@@ -89,7 +101,14 @@ __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ lo
     if (f[k]) index[pre + (uint32_t)__popcll(b & below)] = base + k * 256 + threadIdx.x;
     for (int w = 0; w < 4; ++w) run += s_cnt[k * 4 + w];
   }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = run;
 }
+
+// Planes per thread of the gather: their loads are in flight together, and
+// the planes' groups are the grid's second dimension.  59 planes of 270 k
+// kept Gaussians (135 MB, 28 us at the copy rate): 28.9 us, 37.8 with one
+// thread for all planes.
+constexpr int kGatherPlanes = 8;
 
 __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ src, int64_t src_ld,
                                                 int planes, const int32_t* __restrict__ index,
@@ -97,8 +116,23 @@ __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ src, i
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= m) return;
   const int64_t i = index[j];
-  for (int p = 0; p < planes; ++p) dst[p * dst_ld + j] = src[p * src_ld + i];
+  const int p0 = (int)blockIdx.y * kGatherPlanes;
+  const int count = min(kGatherPlanes, planes - p0);
+  src += (int64_t)p0 * src_ld + i;
+  dst += (int64_t)p0 * dst_ld + j;
+  float x[kGatherPlanes];
+#pragma unroll
+  for (int p = 0; p < kGatherPlanes; ++p)
+    if (p < count) x[p] = src[p * src_ld];
+#pragma unroll
+  for (int p = 0; p < kGatherPlanes; ++p)
+    if (p < count) dst[p * dst_ld] = x[p];
 }
+
+// Chunks up to which the second launch adds the counts up itself, in us with
+// and without the scan: 0.3 M Gaussians 21.4 / 19.6, 4 M 30.8 / 28.5, 8 M
+// 45.6 / 46.8 (the additions grow with the square).
+constexpr int kSumChunks = 4096;
 
 }  // namespace
 
@@ -112,25 +146,31 @@ double opacity_logit_threshold(float min_opacity) {
   return std::log(m / (1.0 - m));
 }
 
-const uint32_t* launch_keep_low_opacity(const float* logit, int n, double thr, int32_t* index,
-                                        void* ws, hipStream_t s) {
+void launch_keep_low_opacity(const float* logit, int n, double thr, int32_t* index, void* ws,
+                             uint32_t* total, hipStream_t s) {
   const int nb = (n + kChunk - 1) / kChunk;
+  if (nb == 0) return;
   uint32_t* counts = static_cast<uint32_t*>(ws);
   StageScope scope(kStCompact, s);
-  if (nb > 0) hipLaunchKernelGGL(k_keep_count, dim3(nb), dim3(256), 0, s, logit, n, thr, counts);
-  hipLaunchKernelGGL(k_keep_scan, dim3(1), dim3(1024), 0, s, counts, nb);
-  if (nb > 0)
-    hipLaunchKernelGGL(k_keep_write, dim3(nb), dim3(256), 0, s, logit, n, thr,
-                       (const uint32_t*)counts, index);
-  return counts + nb;  // the total number kept
+  hipLaunchKernelGGL(k_keep_count, dim3(nb), dim3(256), 0, s, logit, n, thr, counts);
+  const bool sum = nb <= kSumChunks;
+  if (!sum) hipLaunchKernelGGL(k_keep_scan, dim3(1), dim3(1024), 0, s, counts, nb);
+  hipLaunchKernelGGL(sum ? k_keep_write<true> : k_keep_write<false>, dim3(nb), dim3(256), 0, s,
+                     logit, n, thr, (const uint32_t*)counts, index, total);
 }
 
 void launch_gather(const float* src, int64_t src_ld, int planes, const int32_t* index, int m,
                    float* dst, int64_t dst_ld, hipStream_t s) {
   if (m <= 0 || planes <= 0) return;
   StageScope scope(kStCompact, s);
-  hipLaunchKernelGGL(k_gather, dim3((m + 255) / 256), dim3(256), 0, s, src, src_ld, planes, index,
-                     m, dst, dst_ld);
+  // a grid's second dimension holds 65,535 groups of planes
+  constexpr int64_t kMost = 65535 * kGatherPlanes;
+  for (int64_t p = 0; p < planes; p += kMost) {
+    const int count = (int)std::min<int64_t>(kMost, planes - p);
+    const dim3 grid((m + 255) / 256, (count + kGatherPlanes - 1) / kGatherPlanes);
+    hipLaunchKernelGGL(k_gather, grid, dim3(256), 0, s, src + p * src_ld, src_ld, count, index, m,
+                       dst + p * dst_ld, dst_ld);
+  }
 }
 
 }  // namespace gs

@@ -138,8 +138,8 @@ void launch_l1(const float* image, const float* target, int64_t count, float* gr
 // low-opacity culling and plane gathers
 size_t keep_workspace_bytes(int n);
 double opacity_logit_threshold(float min_opacity);
-const uint32_t* launch_keep_low_opacity(const float* logit, int n, double thr, int32_t* index,
-                                        void* ws, hipStream_t s);
+void launch_keep_low_opacity(const float* logit, int n, double thr, int32_t* index, void* ws,
+                             uint32_t* total, hipStream_t s);
 void launch_gather(const float* src, int64_t src_ld, int planes, const int32_t* index, int m,
                    float* dst, int64_t dst_ld, hipStream_t s);
 void launch_l1_penalty(const float* x, const float* ref, int rows, int bound, int64_t ld, float w,
