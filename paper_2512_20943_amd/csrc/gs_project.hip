@@ -510,11 +510,35 @@ __global__ __launch_bounds__(256) void k_project_bwd(
 
   float st_acc = 0.f;
   uint32_t st_cnt = 0;
-  for (int v = 0; v < n_views; ++v) {
+  // A view's records are loaded while the view before it is computed (and its
+  // flags a view earlier still): with two waves per SIMD the loop otherwise
+  // waits for two dependent loads per view.  300 k Gaussians in 20 views 195
+  // -> 169 us, 2 M in 8 views 484 -> 384 (214 at the copy rate for its 1.0
+  // GB), 300 k in one view 32.5 -> 32.9.
+  struct {
+    float4 ga, gb, gc;
+    float A, B, C;
+  } next{};
+  auto load_view = [&](int v) {
     const size_t j = (size_t)v * L + i;
-    const uint8_t fl = flags[j];
+    next.ga = g2d[3 * j + 0];
+    next.gb = g2d[3 * j + 1];
+    next.gc = g2d[3 * j + 2];
+    const float* s = reinterpret_cast<const float*>(splat + kSplatF4 * j);
+    next.A = s[2];
+    next.B = s[3];
+    next.C = s[4];
+  };
+  uint8_t fl_next = n_views > 0 ? flags[i] : 0, fl_after = n_views > 1 ? flags[L + i] : 0;
+  if (fl_next & kVisible) load_view(0);
+  for (int v = 0; v < n_views; ++v) {
+    const auto now = next;
+    const uint8_t fl = fl_next;
+    fl_next = fl_after;
+    if (v + 2 < n_views) fl_after = flags[(size_t)(v + 2) * L + i];
+    if (v + 1 < n_views && (fl_next & kVisible)) load_view(v + 1);
     if (!(fl & kVisible)) continue;
-    const float4 ga = g2d[3 * j + 0], gb = g2d[3 * j + 1], gc = g2d[3 * j + 2];
+    const float4 ga = now.ga, gb = now.gb, gc = now.gc;
     const float g_px = ga.x, g_py = ga.y, g_A = ga.z, g_B = ga.w, g_C = gb.x, g_al = gb.y;
     st_acc += sqrtf(g_px * g_px + g_py * g_py);
     ++st_cnt;
@@ -572,9 +596,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(
     float gz = -(g_px * fx * x0 + g_py * fy * x1) * iz2;
 
     // conic -> 2D covariance: G_S = -Q G_Q Q, G_Q = [[gA, gB/2], [gB/2, gC]]
-    const float4 s0 = splat[kSplatF4 * j + 0];
-    const float4 s1 = splat[kSplatF4 * j + 1];
-    const float A = s0.z, B = s0.w, C = s1.x;
+    const float A = now.A, B = now.B, C = now.C;
     const float q00 = A * g_A + B * 0.5f * g_B, q01 = A * 0.5f * g_B + B * g_C;
     const float q10 = B * g_A + C * 0.5f * g_B, q11 = B * 0.5f * g_B + C * g_C;
     const float G00 = -(q00 * A + q01 * B), G01 = -(q00 * B + q01 * C);
