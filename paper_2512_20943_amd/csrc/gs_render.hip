@@ -120,7 +120,8 @@ __device__ __forceinline__ uint32_t quadrant_mask(float4 s0, float4 s1, float4 s
   return m;
 }
 
-// The same for the one quadrant at (ox, oy).
+// The same for the one quadrant at (ox, oy), or for its ROWS rows from oy on.
+template <int ROWS = 8>
 __device__ __forceinline__ bool quadrant_hit(float4 s0, float4 s1, float4 s2, float ox, float oy) {
   const float A = s0.z, B = s0.w, C = s1.x, dq = s2.z, op = s1.y;
   // alpha >= 1/255  <=>  q <= 2 ln(255 opacity)
@@ -130,7 +131,8 @@ __device__ __forceinline__ bool quadrant_hit(float4 s0, float4 s1, float4 s2, fl
   const float iA = __builtin_amdgcn_rcpf(A), iC = __builtin_amdgcn_rcpf(C);
   const float r1 = B * iA, r2 = B * iC, dA = dq * iA, dC = dq * iC;
   const float u0 = ox - s0.x, v0 = oy - s0.y;
-  return thr > 0.f && box_min_q(A, C, r1, r2, dA, dC, u0, u0 + 7.f, v0, v0 + 7.f) <= thr;
+  return thr > 0.f &&
+         box_min_q(A, C, r1, r2, dA, dC, u0, u0 + 7.f, v0, v0 + (float)(ROWS - 1)) <= thr;
 }
 
 // Bits 0 and 1 set when some pixel of the quadrant at (ox, oyq), resp.
@@ -735,6 +737,169 @@ __global__ __launch_bounds__(256) void k_render_fwd_quads(
                         n_contrib + pix * v, &o);
 }
 
+// ---------------------------------------------------------------- forward,
+// two waves per quadrant
+// The forward for launches of few tiles, where the longest list's serial chain
+// is all that counts and a wave has a SIMD to itself.  A tile is a workgroup
+// of eight waves, one per 8x4 half of a quadrant: a half needs fewer entries
+// than its quadrant, and its 32 pixels leave the wave's halves of lanes to
+// two entries.  Lanes l and l + 32 hold the same pixel: each evaluates the
+// alpha of one entry of a pair, a lane swap gives both to both, and both
+// composite the pair in order, with the arithmetic of the other kernels:
+// bit-identical outputs, the L1 sums included.
+struct OctPlace {
+  int x0, y0;      // this lane's pixel in the tile's upper left quadrant
+  int dx, dy;      // offset of the quadrant
+  int oy;          // first row of the half in the quadrant
+};
+
+__device__ __forceinline__ OctPlace oct_place(int wave, int lane) {
+  OctPlace o;
+  o.oy = 4 * (wave & 1);
+  o.x0 = lane & 7;
+  o.y0 = o.oy + ((lane & 31) >> 3);
+  o.dx = 8 * ((wave >> 1) & 1);
+  o.dy = 8 * (wave >> 2);
+  return o;
+}
+
+// The values of lane l and of lane l + 32 of a pair, on both.
+__device__ __forceinline__ void both_halves(float x, float& lower, float& upper) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                  false);
+  lower = __uint_as_float(p[0]);
+  upper = __uint_as_float(p[1]);
+}
+
+template <bool CLAMP>
+__device__ __forceinline__ void oct_walk(const QuadStage& st, int count, float fx0, float fy0,
+                                         float offx, float offy, QuadPixel& px) {
+  const int half = (threadIdx.x & 63) >> 5;
+  for (int i0 = 0; i0 < count && px.live != 0; i0 += 4) {
+    float alpha[4];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const float4 ra = st.a[i0 + 2 * p + half];
+      const float2 rb = *reinterpret_cast<const float2*>(&st.b[i0 + 2 * p + half]);
+      const float dx = (ra.x - fx0) - offx, dy = (ra.y - fy0) - offy;
+      const float ea = eval_ea(ra, row_q(make_float4(rb.x, rb.y, 0.f, 0.f), dy), dx, dy);
+      both_halves(CLAMP ? fminf(kAlphaMax, ea) : ea, alpha[2 * p], alpha[2 * p + 1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(alpha[i]));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned long long use =
+          px.live & __builtin_amdgcn_ballot_w64(alpha[i] >= kAlphaMin);
+      if (use == 0) continue;
+      const float2 rg = *reinterpret_cast<const float2*>(&st.b[i0 + i].z);
+      const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
+      const float Tn = px.T * (1.f - alpha[i]);
+      const unsigned long long stop = use & __builtin_amdgcn_ballot_w64(Tn < kTStop);
+      const unsigned long long cm = use & ~stop;
+      const bool comp = __builtin_amdgcn_inverse_ballot_w64(cm);
+      px.live &= ~stop;
+      const float wt = comp ? alpha[i] * px.T : 0.f;
+      px.c0 = fmaf(rg.x, wt, px.c0);
+      px.c1 = fmaf(rg.y, wt, px.c1);
+      px.c2 = fmaf(c.x, wt, px.c2);
+      px.T = comp ? Tn : px.T;
+      px.last = comp ? __float_as_int(c.y) : px.last;
+    }
+  }
+}
+
+template <bool L1>
+__global__ __launch_bounds__(512) void k_render_fwd_octs(
+    const float4* __restrict__ splat, int ld, const uint32_t* __restrict__ vals,
+    const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
+    float bg1, float bg2, float* __restrict__ image, float* __restrict__ final_T,
+    int32_t* __restrict__ n_contrib, const float* __restrict__ target, float* __restrict__ grad,
+    float inv_count, double* __restrict__ partial) {
+  __shared__ QuadStage sh[8];
+  const int seg = blockIdx.x;
+  const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
+  const int ty = tile / TX, tx = tile - ty * TX;
+  const size_t pix = (size_t)W * H;
+  const float4* sv = splat + kSplatF4 * (size_t)v * ld;
+  const uint2 rg = ranges[seg];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const OctPlace at = oct_place(wave, lane);
+  const int xl = tx * kTile + at.x0, yl = ty * kTile + at.y0;
+  const int x = xl + at.dx, y = yl + at.dy;
+  const float fx0 = (float)xl, fy0 = (float)yl;
+  const float offx = (float)at.dx, offy = (float)at.dy;
+  const float ox = (float)(tx * kTile + at.dx), oy = (float)(ty * kTile + at.dy + at.oy);
+  const bool inside = x < W && y < H;
+  QuadPixel px{1.f, 0.f, 0.f, 0.f, 0, __builtin_amdgcn_ballot_w64(inside)};
+  uint32_t e = rg.x + (uint32_t)lane;
+  float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0, q2 = q0;
+  auto load = [&](uint32_t g) {
+    const float4* r = sv + kSplatF4 * (size_t)g;
+    q0 = r[0];
+    q1 = r[1];
+    q2 = r[2];
+  };
+  if (e < rg.y) load(vals[e]);
+  uint32_t gn = e + 64 < rg.y ? vals[e + 64] : 0u;  // the next batch's id
+  QuadStage& st = sh[wave];
+  for (uint32_t b0 = rg.x; b0 < rg.y && px.live != 0; b0 += 64, e += 64) {
+    const bool hit = e < rg.y && quadrant_hit<4>(q0, q1, q2, ox, oy);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    const int count = (int)__popcll(m);
+    quad_stage(st, q0, q1, q2, hit, lanes_below(m), count, (int)(e - rg.x) + 1);
+    const bool clamp = __builtin_amdgcn_ballot_w64(hit && !(q1.y < 0.98f)) != 0;
+    if (e + 64 < rg.y) load(gn);
+    gn = e + 128 < rg.y ? vals[e + 128] : 0u;
+    wave_lds_fence();
+    if (clamp)
+      oct_walk<true>(st, count, fx0, fy0, offx, offy, px);
+    else
+      oct_walk<false>(st, count, fx0, fy0, offx, offy, px);
+    wave_lds_fence();
+  }
+  float4 dabs = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (inside && lane < 32) {
+    const size_t p = (size_t)y * W + x;
+    const float o[3] = {px.c0 + px.T * bg0, px.c1 + px.T * bg1, px.c2 + px.T * bg2};
+    if (!L1 || image) {
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) image[3 * pix * v + ch * pix + p] = o[ch];
+    }
+    if constexpr (L1) {
+      float d[3];
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        d[ch] = o[ch] - target[3 * pix * v + ch * pix + p];
+        grad[3 * pix * v + ch * pix + p] = d[ch] > 0.f ? inv_count : (d[ch] < 0.f ? -inv_count : 0.f);
+      }
+      dabs = make_float4(fabsf(d[0]), fabsf(d[1]), fabsf(d[2]), 0.f);
+    }
+    final_T[pix * v + p] = px.T;
+    n_contrib[pix * v + p] = px.last;
+  }
+  if constexpr (L1) {
+    // the tile's sum in render_tile_fwd's order: per lane of a quadrant over
+    // the quadrants, then over the lanes
+    if (lane < 32) st.a[lane] = dabs;
+    __syncthreads();
+    if (wave == 0) {
+      double l1sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float4 d = sh[2 * w + (lane >> 5)].a[lane & 31];
+        l1sum += (double)d.x;
+        l1sum += (double)d.y;
+        l1sum += (double)d.z;
+      }
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) l1sum += __shfl_xor(l1sum, off, 64);
+      if (lane == 0) partial[seg] = l1sum;
+    }
+  }
+}
+
 // loss += (sum of the per-tile partials) / count in two fixed-order steps:
 // workgroup b adds partials [b chunk, (b + 1) chunk) (each thread a fixed
 // stride pattern, then a tree) and stores the sum over the first of them,
@@ -1335,6 +1500,205 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
   }
 }
 
+// ---------------------------------------------------------------- backward,
+// two waves per quadrant
+// The backward for launches of few tiles, as the forward's: a workgroup of
+// eight waves, one per 8x4 half of a quadrant, lanes l and l + 32 on the same
+// pixel with one entry of a pair each, back to front.  Three lane swaps give
+// both halves both entries' alpha, reciprocal and colour product, so that the
+// transmittance and the colour behind advance by the pair; the sums over a
+// half's 32 pixels take 10 instructions per entry.
+struct OctBwdShared {
+  QuadStage st[8];
+  float acc[2][8][kQuadSlots * kQuadAcc];
+  int8_t slot[2][8][64];           // an entry's packed slot in a half, or -1
+  unsigned long long seen[2][8];   // with COUNT, entries a half evaluated
+  int wmax[8];
+};
+
+template <bool COUNT>
+__global__ __launch_bounds__(512) void k_render_bwd_octs(
+    const float4* __restrict__ splat, int ld, const uint32_t* __restrict__ vals,
+    const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
+    float bg1, float bg2, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
+    const float* __restrict__ dL_dimage, float* __restrict__ rows,
+    unsigned long long* __restrict__ cnt) {
+  __shared__ OctBwdShared sh;
+  const int seg = blockIdx.x;
+  const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
+  const int ty = tile / TX, tx = tile - ty * TX;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint2 rg = ranges[seg];
+  const float4* sv = splat + kSplatF4 * (size_t)v * ld;
+  const size_t pix = (size_t)W * H;
+  const OctPlace place = oct_place(wave, lane);
+  const int xl = tx * kTile + place.x0, yl = ty * kTile + place.y0;
+  const int x = xl + place.dx, y = yl + place.dy;
+  const float fx0 = (float)xl, fy0 = (float)yl;
+  const float offx = (float)place.dx, offy = (float)place.dy;
+  const float ox = (float)(tx * kTile + place.dx), oy = (float)(ty * kTile + place.dy + place.oy);
+  const bool upper = lane >= 32;  // evaluates the second entry of a pair
+  float T = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+  int nc = 0;
+  if (x < W && y < H) {
+    const size_t p = (size_t)y * W + x;
+    const float* gi = dL_dimage + 3 * pix * v;
+    T = final_T[pix * v + p];
+    nc = n_contrib[pix * v + p];
+    g0 = gi[p];
+    g1 = gi[pix + p];
+    g2 = gi[2 * pix + p];
+  }
+  // dL/dcolour . (the colour composited behind the current entry)
+  float S = g0 * bg0 + g1 * bg1 + g2 * bg2;
+  const int wmax = __builtin_amdgcn_readfirstlane(wave_max(nc));
+  if (lane == 0) sh.wmax[wave] = wmax;
+  __syncthreads();
+  int jm = 0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) jm = max(jm, sh.wmax[w]);
+  const int jmax = __builtin_amdgcn_readfirstlane(jm);
+  // where the sums of an entry end up (wave_sums9x4): its value, and the
+  // lanes that store one
+  const bool u3 = lane & 8, u2 = lane & 4, u1 = lane & 2, u0 = lane & 1;
+  const int acc_lane = (lane & 32 ? (lane & 16 ? 3 : 1) : (lane & 16 ? 2 : 0)) * kQuadAcc +
+                       (u0 ? 8 : 4 * (int)u1 + 2 * (int)u2 + (int)u3);
+  const bool acc_writer = !u0 || (lane & 15) == 1;
+  QuadStage& st = sh.st[wave];
+  // lane k holds the record of entry lo + k of the batch that ends at hi
+  float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0, q2 = q0, q3 = q0;
+  auto load = [&](uint32_t g) {
+    const float4* r = sv + kSplatF4 * (size_t)g;
+    q0 = r[0];
+    q1 = r[1];
+    q2 = r[2];
+    q3 = r[3];
+  };
+  auto id_of = [&](int hi) {  // this lane's entry in the batch that ends at hi
+    const int lo = max(hi - 64, 0);
+    return lo + lane < hi ? vals[rg.x + (uint32_t)(lo + lane)] : 0u;
+  };
+  if (jmax > 0) load(id_of(jmax));
+  uint32_t gn = jmax > 64 ? id_of(jmax - 64) : 0u;
+  int buf = 0, turn = 0;
+  unsigned long long wk_staged = 0, wk_visits = 0, wk_slots = 0, wk_used = 0;
+  for (int hi = jmax; hi > 0; hi -= 64, buf ^= 1, turn = (turn + 1) & 7) {
+    const int lo = max(hi - 64, 0);
+    const bool have = lo + lane < hi;
+    const bool hit = have && lo + lane < wmax && quadrant_hit<4>(q0, q1, q2, ox, oy);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    const int count = (int)__popcll(m);
+    // packed back to front
+    const int slot = count - 1 - lanes_below(m);
+    quad_stage(st, q0, q1, q2, hit, slot, count, lo + lane);
+    sh.slot[buf][wave][lane] = (int8_t)(hit ? slot : -1);
+    // what the flush of this batch needs of the records, kept while the next
+    // batch's are loaded
+    const float fA = q0.z, fB = q0.w, fC = q1.x;
+    const float fr1 = fB * __builtin_amdgcn_rcpf(fA), fiop = __builtin_amdgcn_rcpf(q1.y);
+    const uint32_t frow = instance_row(q3, tx, ty);
+    if (hi > 64) load(gn);
+    gn = hi > 128 ? id_of(hi - 128) : 0u;
+    wave_lds_fence();
+    if constexpr (COUNT) {
+      if (lane == 0) sh.seen[buf][wave] = m;
+    }
+    float* acc = sh.acc[buf][wave];
+    for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
+      float gr[2][9];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int at = i0 + 2 * p + (int)upper;
+        const float4 a = st.a[at], b = st.b[at];
+        const float2 c = *reinterpret_cast<const float2*>(&st.c[at]);
+        const float dx = (a.x - fx0) - offx, dy = (a.y - fy0) - offy;
+        const float t = fmaf(a.w, dy, dx);
+        const float ea = __builtin_amdgcn_exp2f(fmaf(a.z * t, t, fmaf(b.x, dy * dy, b.y)));
+        const float alpha = fminf(kAlphaMax, ea);
+        const bool use = __float_as_int(c.y) < nc && alpha >= kAlphaMin;
+        if constexpr (COUNT) wk_used += (unsigned long long)__popcll(__ballot(use));
+        const float au = use ? alpha : 0.f;
+        float au0, au1, ra0, ra1, gc0, gc1;
+        both_halves(au, au0, au1);
+        both_halves(__builtin_amdgcn_rcpf(1.f - au), ra0, ra1);
+        both_halves(fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z)), gc0, gc1);
+        // the pair in order, on every lane; each half keeps its own entry's
+        const float T0 = T * ra0;
+        T = T0 * ra1;
+        const float d0 = gc0 - S;
+        S = fmaf(au0, d0, S);
+        const float d1 = gc1 - S;
+        S = fmaf(au1, d1, S);
+        const float wt = au * (upper ? T : T0);
+        const float gcb = upper ? d1 : d0;
+        const float gp = ea < kAlphaMax ? wt * gcb : 0.f;
+        const float pt = gp * t;
+        gr[p][0] = pt;
+        gr[p][1] = gp * dy;
+        gr[p][2] = pt * t;
+        gr[p][3] = pt * dy;
+        gr[p][4] = gr[p][1] * dy;
+        gr[p][5] = gp;
+        gr[p][6] = g0 * wt;
+        gr[p][7] = g1 * wt;
+        gr[p][8] = g2 * wt;
+      }
+      // rows 0 and 1 of the wave hold the first entries' pixels, rows 2 and 3
+      // the second ones'
+      float y9[9];
+#pragma unroll
+      for (int cc = 0; cc < 9; ++cc) y9[cc] = pair_rows(gr[0][cc], gr[1][cc]);
+      // the padding's sums go to slots that no entry has
+      const float rs = row_sums9(y9, u1, u0);
+      if (acc_writer) acc[i0 * kQuadAcc + acc_lane] = rs;
+    }
+    __syncthreads();
+    if constexpr (COUNT) {
+      if (wave == 0) {
+        wk_staged += (unsigned long long)(hi - lo);
+        unsigned long long any = 0;
+#pragma unroll
+        for (int w = 0; w < 8; w += 2) {
+          const unsigned long long q = sh.seen[buf][w] | sh.seen[buf][w + 1];
+          wk_slots += (unsigned long long)__popcll(q);  // per quadrant
+          any |= q;
+        }
+        wk_visits += (unsigned long long)__popcll(any);
+      }
+    }
+    if (wave == turn && have) {
+      float mom[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        const int at = sh.slot[buf][w][lane];
+        if (at >= 0) {
+          const float* a = sh.acc[buf][w] + at * kQuadAcc;
+#pragma unroll
+          for (int cc = 0; cc < 9; ++cc) mom[cc] += a[cc];
+        }
+      }
+      write_grad_row(rows + (size_t)frow * kRowFloats, mom, fr1, fA, fB, fC, fiop);
+    }
+  }
+  // entries behind every pixel's last contributor carry zero gradient
+  const int n_entries = (int)(rg.y - rg.x);
+  for (int j = jmax + (int)threadIdx.x; j < n_entries; j += 512) {
+    const uint32_t g = vals[rg.x + (uint32_t)j];
+    float* dst = rows + (size_t)instance_row(sv[kSplatF4 * (size_t)g + 3], tx, ty) * kRowFloats;
+#pragma unroll
+    for (int cc = 0; cc < 9; ++cc) dst[cc] = 0.f;
+  }
+  if constexpr (COUNT) {
+    if (lane == 0) {
+      atomicAdd(cnt + kWkBwdStaged, wk_staged);
+      atomicAdd(cnt + kWkBwdVisits, wk_visits);
+      atomicAdd(cnt + kWkBwdSlots, wk_slots);
+      atomicAdd(cnt + kWkBwdUsed, wk_used);
+    }
+  }
+}
+
 // One step of a segmented inclusive scan of nine values over the wave: add
 // the value of the lane CTRL names when it carries the same pair index q.
 // q does not decrease over the lanes, so equal ends mean that every lane in
@@ -1453,6 +1817,12 @@ constexpr int64_t kQuadBatchTiles = 66000;
 // instances) 73 -> 53, 1,200 tiles (0.65 M) 233 -> 161, 3,813 tiles (0.41 M)
 // 122 -> 115, 3,600 tiles (1.1 M) 209 -> 244, 10,880 tiles 398 -> 586.
 constexpr int kQuadBwdTiles = 2400;
+// Most tiles of a forward or backward launch that runs two waves per
+// quadrant.  render_fwd with the L1 term / render_bwd, one wave per quadrant
+// -> two, in us: 64 tiles 81 / 110 -> 59 / 84, 256 tiles 39 / 48 -> 32 / 39,
+// 500 tiles (0.48 M instances) 76 / 130 -> 65 / 109, 750 tiles 43 / 71 -> 43 /
+// 68, 960 tiles 31 / 47 -> 31 / 51, 1,200 tiles (0.65 M) 70 / 163 -> 81 / 163.
+constexpr int kOctTiles = 640;
 }  // namespace
 
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
@@ -1474,7 +1844,8 @@ void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, g_work);
   else if (blocks <= kQuadFwdTiles)
-    hipLaunchKernelGGL(k_render_fwd_quads<false>, dim3(blocks), dim3(256), 0, s,
+    hipLaunchKernelGGL(blocks <= kOctTiles ? k_render_fwd_octs<false> : k_render_fwd_quads<false>,
+                       dim3(blocks), dim3(blocks <= kOctTiles ? 512 : 256), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, (const float*)nullptr, (float*)nullptr,
@@ -1508,7 +1879,8 @@ void launch_render_fwd_l1(const gs_projected& proj, const gs_tile_lists& lists, 
                        bg[2], image, final_T, n_contrib, target, grad, (float)(1.0 / count),
                        partial, g_work);
   else if (blocks <= kQuadFwdTiles)
-    hipLaunchKernelGGL(k_render_fwd_quads<true>, dim3(blocks), dim3(256), 0, s,
+    hipLaunchKernelGGL(blocks <= kOctTiles ? k_render_fwd_octs<true> : k_render_fwd_quads<true>,
+                       dim3(blocks), dim3(blocks <= kOctTiles ? 512 : 256), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, target, grad, (float)(1.0 / count),
@@ -1566,10 +1938,11 @@ void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int
   if (blocks == 0) return;
   {
     StageScope scope(kStRenderBwd, s);
-    const bool quads = blocks <= kQuadBwdTiles;
-    auto kernel = quads ? (g_work ? k_render_bwd_quads<true> : k_render_bwd_quads<false>)
-                        : (g_work ? k_render_bwd<true> : k_render_bwd<false>);
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(quads ? 256 : 64), 0, s,
+    const bool octs = blocks <= kOctTiles, quads = blocks <= kQuadBwdTiles;
+    auto kernel = octs    ? (g_work ? k_render_bwd_octs<true> : k_render_bwd_octs<false>)
+                  : quads ? (g_work ? k_render_bwd_quads<true> : k_render_bwd_quads<false>)
+                          : (g_work ? k_render_bwd<true> : k_render_bwd<false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(octs ? 512 : quads ? 256 : 64), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], final_T, n_contrib, dL_dimage, rows, g_work);
