@@ -746,7 +746,9 @@ __global__ __launch_bounds__(256) void k_render_fwd_quads(
 // two entries.  Lanes l and l + 32 hold the same pixel: each evaluates the
 // alpha of one entry of a pair, a lane swap gives both to both, and both
 // composite the pair in order, with the arithmetic of the other kernels:
-// bit-identical outputs, the L1 sums included.
+// bit-identical outputs, the L1 sums included.  The walk has no branch per
+// entry: with a wave alone on its SIMD a skipped entry costs less than the
+// branch (64 tiles 58.3 -> 52.7 us).
 struct OctPlace {
   int x0, y0;      // this lane's pixel in the tile's upper left quadrant
   int dx, dy;      // offset of the quadrant
@@ -791,7 +793,6 @@ __device__ __forceinline__ void oct_walk(const QuadStage& st, int count, float f
     for (int i = 0; i < 4; ++i) {
       const unsigned long long use =
           px.live & __builtin_amdgcn_ballot_w64(alpha[i] >= kAlphaMin);
-      if (use == 0) continue;
       const float2 rg = *reinterpret_cast<const float2*>(&st.b[i0 + i].z);
       const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
       const float Tn = px.T * (1.f - alpha[i]);
@@ -924,6 +925,27 @@ __global__ __launch_bounds__(256) void k_l1_chunk_sum(double* __restrict__ parti
   if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
   __syncthreads();
   if (threadIdx.x == 0 && b0 < n) partial[b0] = (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+// The same in one workgroup, for partials that one CU reads in no time.
+__global__ __launch_bounds__(1024) void k_l1_total(const double* __restrict__ partial, uint32_t n,
+                                                   double inv_count, double* __restrict__ loss) {
+  __shared__ double s[16];
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  uint32_t i = threadIdx.x;
+  for (; i + 3 * 1024 < n; i += 4 * 1024) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[u] += partial[i + u * 1024];
+  }
+  for (int u = 0; i < n; i += 1024, ++u) a[u] += partial[i];
+  double acc = (a[0] + a[1]) + (a[2] + a[3]);
+  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  acc = threadIdx.x < 16 ? s[threadIdx.x] : 0.0;
+  for (int off = 8; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if (threadIdx.x == 0) atomicAdd(loss, acc * inv_count);
 }
 
 __global__ __launch_bounds__(64) void k_l1_chunks_total(const double* __restrict__ partial,
@@ -1819,10 +1841,15 @@ constexpr int64_t kQuadBatchTiles = 66000;
 constexpr int kQuadBwdTiles = 2400;
 // Most tiles of a forward or backward launch that runs two waves per
 // quadrant.  render_fwd with the L1 term / render_bwd, one wave per quadrant
-// -> two, in us: 64 tiles 81 / 110 -> 59 / 84, 256 tiles 39 / 48 -> 32 / 39,
+// -> two, in us: 64 tiles 81 / 110 -> 55 / 84, 256 tiles 39 / 48 -> 31 / 39,
 // 500 tiles (0.48 M instances) 76 / 130 -> 65 / 109, 750 tiles 43 / 71 -> 43 /
-// 68, 960 tiles 31 / 47 -> 31 / 51, 1,200 tiles (0.65 M) 70 / 163 -> 81 / 163.
+// 68, 960 tiles 31 / 47 -> 32 / 51, 1,200 tiles (0.65 M) 70 / 163 -> 81 / 163.
 constexpr int kOctTiles = 640;
+// Most tiles whose loss partials one workgroup adds up, in place of a launch
+// of 64 and one of one: render_fwd with the L1 term, two launches -> one, 64
+// tiles 60.1 -> 58.3 us, 3,813 tiles 54.0 -> 50.9, 7,752 tiles 125.3 -> 123.7,
+// 32,640 tiles 550 -> 560.
+constexpr int kL1OneTiles = 8192;
 }  // namespace
 
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
@@ -1891,6 +1918,11 @@ void launch_render_fwd_l1(const gs_projected& proj, const gs_tile_lists& lists, 
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, target, grad, (float)(1.0 / count),
                        partial, nullptr);
+  if (blocks <= kL1OneTiles) {
+    hipLaunchKernelGGL(k_l1_total, dim3(1), dim3(1024), 0, s, (const double*)partial,
+                       (uint32_t)blocks, 1.0 / count, loss);
+    return;
+  }
   const uint32_t chunk = ((uint32_t)blocks + kL1Chunks - 1) / kL1Chunks;
   const uint32_t n_chunks = ((uint32_t)blocks + chunk - 1) / chunk;
   hipLaunchKernelGGL(k_l1_chunk_sum, dim3(n_chunks), dim3(256), 0, s, partial, (uint32_t)blocks,

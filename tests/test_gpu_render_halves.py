@@ -82,3 +82,18 @@ def test_backward_agrees(views, k):
         for q in range(9):
             a, b = part[:, :, q], whole[v:v + k, :, q]
             assert (a - b).norm() <= 2.5e-5 * b.norm(), f"column {q} of view {v}"
+
+
+@pytest.mark.parametrize("k", [1, 9, 20, 40])
+def test_l1_sum_over_tiles(views, k):
+    """The loss of 121 k tiles (1,089: a second step of the one workgroup that
+    adds the partials, 4,840: its unrolled steps)."""
+    name, r, g, cams = views
+    print(f"l1 sum {name} {k}", flush=True)
+    c = cams.slice(0, k)
+    target = torch.rand(k, 3, H, W, generator=torch.Generator("cuda").manual_seed(k), device="cuda")
+    loss = torch.full((1,), 0.5, dtype=torch.float64, device="cuda")
+    out = r.forward_l1(g, c, target, torch.empty_like(target), loss, keep_image=True)
+    want = 0.5 + float((out["image"] - target).abs().double().mean())
+    # FP64 sums of the same FP32 differences
+    assert abs(float(loss) - want) <= 1e-12
