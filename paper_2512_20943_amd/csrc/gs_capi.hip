@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cmath>
 #include <cstring>
+#include <chrono>
 #include <new>
 
 #include <vector>
@@ -399,6 +400,19 @@ static gs_status check_ws_align(gs_ctx* c, const void* ws) {
   return GS_OK;
 }
 
+// Waits up to a millisecond for a word that the device sets in host memory.
+// A wait for an event behind the same kernel came back 35 us later.
+static bool wait_flag(const uint32_t* flag) {
+  const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+  do {
+    for (int k = 0; k < 32; ++k) {
+      if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != 0) return true;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() < end);
+  return false;
+}
+
 gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
                       const gs_camera* cd, int V, gs_tile_lists* lists, void* ws, size_t ws_bytes,
                       void* stream) {
@@ -433,14 +447,23 @@ gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
   if (proj->n > 0) {
     e = gs::bin_sort_stage1(plan, *proj, cd, ws, stats, s);
     if (e != hipSuccess) return hip_fail(c, e, "bin_sort (count)");
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+    // the device goes on while the host reads the counts
+    bool ahead = false;
+    e = gs::bin_sort_ahead(plan, *proj, *lists, ws, &ahead, s);
+    if (e != hipSuccess) return hip_fail(c, e, "bin_sort (fill)");
+    if (!ahead || !wait_flag(stats + gs::kCountsReady)) {
+      e = hipStreamSynchronize(s);
+      if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+    }
   }
   const uint64_t M = (uint64_t)stats[2] | ((uint64_t)stats[3] << 32);
   lists->count = (int64_t)M;
-  if (M > (uint64_t)lists->capacity)
+  if (M > (uint64_t)lists->capacity) {
+    // what was enqueued ahead does nothing, but reads the workspace
+    hipStreamSynchronize(s);
     return fail(c, GS_ERR_CAPACITY, "instance count %llu exceeds capacity %lld",
                 (unsigned long long)M, (long long)lists->capacity);
+  }
   e = gs::bin_sort_stage2(plan, *proj, stats, *lists, ws, s);
   if (e != hipSuccess) return hip_fail(c, e, "bin_sort (sort)");
   return GS_OK;

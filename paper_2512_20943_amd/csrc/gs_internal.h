@@ -104,6 +104,11 @@ size_t bin_sort_workspace_bytes(int n_views, int ld, int64_t capacity, int64_t n
 // written.
 hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
                            const gs_camera* cams_dev, void* ws, uint32_t* stats, hipStream_t s);
+// The word of stats that the direct route's scan sets (system scope) once
+// all the others are written.
+constexpr int kCountsReady = 7;
+hipError_t bin_sort_ahead(const BinSortPlan& p, const gs_projected& proj,
+                          const gs_tile_lists& lists, void* ws, bool* ahead, hipStream_t s);
 hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const uint32_t* stats,
                            gs_tile_lists& lists, void* ws, hipStream_t s);
 size_t usage_masks_workspace_bytes(int n);

@@ -999,16 +999,23 @@ __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uin
 }
 
 // Exclusive scan of the tile counts in place, in one workgroup, with their
-// sum behind the last; the longest list to *longest (host memory).
+// sum behind the last, and to *go whether the lists can be filled and sorted:
+// at most `capacity` instances, no list above kDirectLongest.  The longest
+// list goes to *longest in host memory, and then, when the host may read all
+// that this and the kernels before it wrote there, 1 to *ready.
+constexpr uint32_t kDirectLongest = 4096;  // keys a sorting workgroup holds
 constexpr int kScanBlock = 1024;
 
 __global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__ counts,
-                                                          uint32_t nseg,
-                                                          uint32_t* __restrict__ longest) {
+                                                          uint32_t nseg, uint64_t capacity,
+                                                          uint32_t* __restrict__ longest,
+                                                          uint32_t* __restrict__ ready,
+                                                          uint32_t* __restrict__ go) {
   __shared__ uint32_t s_wave[kScanBlock / 64], s_max[kScanBlock / 64];
   constexpr uint32_t kPer = 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t carry = 0, most = 0;
+  uint64_t all = 0;
   for (uint32_t b0 = 0; b0 < nseg; b0 += kScanBlock * kPer) {
     const uint32_t e0 = b0 + threadIdx.x * kPer;
     uint32_t x[kPer], sum = 0;
@@ -1031,6 +1038,7 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__
       const uint32_t t = s_wave[w];
       if (w < wave) run += t;
       carry += t;
+      all += t;
     }
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) {
@@ -1046,17 +1054,23 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__
     for (int w = 1; w < kScanBlock / 64; ++w) most = max(most, s_max[w]);
     counts[nseg] = carry;
     *longest = most;
+    *go = all <= capacity && most <= kDirectLongest ? 1u : 0u;
+    __threadfence_system();
+    __hip_atomic_store(ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
 // Every instance's Gaussian id to its tile's list, from starts[seg] plus the
-// chunk's place in the column on.  Writes the pairs' bases too.
+// chunk's place in the column on.  Writes the pairs' bases too.  Nothing
+// happens without the scan's go-ahead.
 __global__ __launch_bounds__(kChunkThreads) void k_tile_fill(
     int n, int ld, int V, const int32_t* __restrict__ tiles,
     const uint32_t* __restrict__ chunk_off, uint32_t* __restrict__ splat_words,
     const uint32_t* __restrict__ seg_base, const int32_t* __restrict__ txv,
     const uint32_t* __restrict__ rows, const uint32_t* __restrict__ starts,
-    uint32_t* __restrict__ vals, uint32_t* __restrict__ gv_base) {
+    const uint32_t* __restrict__ go, uint32_t* __restrict__ vals,
+    uint32_t* __restrict__ gv_base) {
+  if (*go == 0) return;
   __shared__ ChunkPairs sh;
   const uint32_t chunk = xcd_chunk();
   for (int v = blockIdx.y; v < V; v += gridDim.y) {
@@ -1220,24 +1234,30 @@ __device__ __forceinline__ void sort_list(uint32_t* __restrict__ list, uint32_t 
 }
 
 // Sorts each tile's list by (depth, id) and writes its range (0, 0 for an
-// empty one).  One workgroup of T threads per tile, lists of at most 16 T.
-template <int T>
+// empty one).  One workgroup of T threads per tile; lists longer than 16 T
+// are left, and with LONG those that one wave sorts.
+constexpr uint32_t kShortList = 16 * 64;
+
+template <int T, bool LONG = false>
 __global__ __launch_bounds__(T) void k_tile_sort(int V, int ld,
                                                  const uint32_t* __restrict__ starts,
                                                  const uint32_t* __restrict__ seg_base,
                                                  const uint32_t* __restrict__ depth_bits,
+                                                 const uint32_t* __restrict__ go,
                                                  uint32_t* __restrict__ vals,
                                                  uint32_t* __restrict__ ranges,
                                                  uint64_t* __restrict__ keys) {
   __shared__ double s_keys[T > 64 ? 16 * T : 1];
+  if (*go == 0) return;
   const uint32_t seg = blockIdx.x;
   const uint32_t start = starts[seg], end = starts[seg + 1];
   const uint32_t count = end - start;
+  if (LONG && count <= kShortList) return;
   if (threadIdx.x == 0) {
     ranges[2 * (size_t)seg] = count > 0 ? start : 0u;
     ranges[2 * (size_t)seg + 1] = count > 0 ? end : 0u;
   }
-  if (count == 0) return;
+  if (count == 0 || count > 16 * T) return;
   int lo = 0, hi = V - 1;  // last view whose base <= seg
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -1246,13 +1266,12 @@ __global__ __launch_bounds__(T) void k_tile_sort(int V, int ld,
   const uint32_t* depth = depth_bits + (size_t)lo * ld;
   uint32_t* list = vals + start;
   uint64_t* lk = keys ? keys + start : nullptr;
-  if (count <= T)
-    sort_list<1, T>(list, count, depth, lk, seg, s_keys);
-  else if (count <= 2 * T)
-    sort_list<2, T>(list, count, depth, lk, seg, s_keys);
-  else if (count <= 4 * T)
-    sort_list<4, T>(list, count, depth, lk, seg, s_keys);
-  else if (count <= 8 * T)
+  if constexpr (!LONG) {
+    if (count <= T) return sort_list<1, T>(list, count, depth, lk, seg, s_keys);
+    if (count <= 2 * T) return sort_list<2, T>(list, count, depth, lk, seg, s_keys);
+    if (count <= 4 * T) return sort_list<4, T>(list, count, depth, lk, seg, s_keys);
+  }
+  if (count <= 8 * T)
     sort_list<8, T>(list, count, depth, lk, seg, s_keys);
   else
     sort_list<16, T>(list, count, depth, lk, seg, s_keys);
@@ -1606,7 +1625,6 @@ struct DirectPlan {
 // 425 -> 428, 6 M (32 M) 704 -> 851: its lists are written word by word, the
 // radix passes write runs.
 constexpr int64_t kDirectPairs = 3000000;
-constexpr uint32_t kDirectLongest = 4096;  // keys a sorting workgroup holds
 
 DirectPlan plan_direct(const BinSortPlan& p, const Layout& L) {
   DirectPlan d{};
@@ -1651,7 +1669,9 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
                        at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), rows);
     hipLaunchKernelGGL(k_tile_columns, dim3(cdiv(nseg, 64u)), dim3(1024), 0, s, p.n_views, nseg,
                        gx, at<uint32_t>(ws, L.seg_base), rows, counts);
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nseg, stats + 6);
+    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nseg,
+                       (uint64_t)p.capacity, stats + 6, stats + kCountsReady,
+                       at<uint32_t>(ws, L.total));
   }
   return hipGetLastError();
 }
@@ -1718,6 +1738,53 @@ void depth_count_emit(const BinSortPlan& p, const gs_projected& proj, const Layo
 }
 }  // namespace
 
+namespace {
+template <typename Kernel>
+void launch_tile_sort(Kernel kernel, int threads, const BinSortPlan& p, const gs_projected& proj,
+                      const DirectPlan& d, const Layout& L, const gs_tile_lists& lists, void* ws,
+                      hipStream_t s) {
+  hipLaunchKernelGGL(kernel, dim3((unsigned)p.n_segments), dim3(threads), 0, s, p.n_views, p.ld,
+                     at<uint32_t>(ws, d.counts), at<uint32_t>(ws, L.seg_base), proj.depth_bits,
+                     at<uint32_t>(ws, L.total), lists.vals, lists.ranges, lists.keys);
+}
+}  // namespace
+
+// Most tiles whose lists four waves sort, whatever their length; beyond, one
+// wave does up to kShortList.  The sort in us, one wave (and four for long
+// lists) -> four: 64 tiles 26.6 -> 12.9, 500 tiles (0.48 M instances) 33.2 ->
+// 17.6, 960 tiles 7.3 -> 7.2, 1,200 tiles 7.4 -> 8.3, 3,813 tiles 10.7 -> 14.8.
+constexpr int64_t kWideSortTiles = 1024;
+
+// The direct route's fill and sort, enqueued before the host has read the
+// counts: the kernels do nothing without the scan's go-ahead.  Beyond
+// kWideSortTiles, lists above kShortList follow in stage 2.  The device was
+// idle for 25 us of a 187 us view while the host read the counts and came
+// back with the rest.
+hipError_t bin_sort_ahead(const BinSortPlan& p, const gs_projected& proj,
+                          const gs_tile_lists& lists, void* ws, bool* ahead, hipStream_t s) {
+  const Layout L = make_layout(p.n_views, p.ld, p.capacity, p.n_segments);
+  const DirectPlan d = plan_direct(p, L);
+  *ahead = d.possible;
+  if (!d.possible) return hipSuccess;
+  {
+    StageScope scope(kStEmit, s);
+    const dim3 grid(cdiv((uint64_t)p.n, kCountChunk),
+                    std::min<uint32_t>((uint32_t)p.n_views, 65535u));
+    hipLaunchKernelGGL(k_tile_fill, grid, dim3(kChunkThreads), 0, s, p.n, p.ld, p.n_views,
+                       proj.tiles_touched, at<uint32_t>(ws, L.iparts),
+                       reinterpret_cast<uint32_t*>(proj.splat), at<uint32_t>(ws, L.seg_base),
+                       at<int32_t>(ws, L.txv), at<uint32_t>(ws, d.rows),
+                       at<uint32_t>(ws, d.counts), at<uint32_t>(ws, L.total), lists.vals,
+                       lists.gv_base);
+  }
+  StageScope scope(kStSegmentSort, s);
+  if (p.n_segments <= kWideSortTiles)
+    launch_tile_sort(k_tile_sort<256>, 256, p, proj, d, L, lists, ws, s);
+  else
+    launch_tile_sort(k_tile_sort<64>, 64, p, proj, d, L, lists, ws, s);
+  return hipGetLastError();
+}
+
 hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const uint32_t* stats,
                            gs_tile_lists& lists, void* ws, hipStream_t s) {
   const uint32_t dmin = stats[0], dmax = stats[1], M = stats[2], N = stats[4];
@@ -1727,24 +1794,10 @@ hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const
     return hipGetLastError();
   }
   const DirectPlan d = plan_direct(p, L);
-  if (d.possible && stats[6] <= kDirectLongest) {
-    const uint32_t* starts = at<uint32_t>(ws, d.counts);
-    {
-      StageScope scope(kStEmit, s);
-      const dim3 grid(cdiv((uint64_t)p.n, kCountChunk),
-                      std::min<uint32_t>((uint32_t)p.n_views, 65535u));
-      hipLaunchKernelGGL(k_tile_fill, grid, dim3(kChunkThreads), 0, s, p.n, p.ld, p.n_views,
-                         proj.tiles_touched, at<uint32_t>(ws, L.iparts),
-                         reinterpret_cast<uint32_t*>(proj.splat), at<uint32_t>(ws, L.seg_base),
-                         at<int32_t>(ws, L.txv), at<uint32_t>(ws, d.rows), starts, lists.vals,
-                         lists.gv_base);
-    }
+  if (d.possible && stats[6] <= kDirectLongest) {  // filled and sorted already
+    if (stats[6] <= kShortList || p.n_segments <= kWideSortTiles) return hipSuccess;
     StageScope scope(kStSegmentSort, s);
-    const bool wide = stats[6] > 1024;
-    hipLaunchKernelGGL(wide ? k_tile_sort<256> : k_tile_sort<64>, dim3((unsigned)p.n_segments),
-                       dim3(wide ? 256 : 64), 0, s, p.n_views, p.ld, starts,
-                       at<uint32_t>(ws, L.seg_base), proj.depth_bits, lists.vals, lists.ranges,
-                       lists.keys);
+    launch_tile_sort(k_tile_sort<256, true>, 256, p, proj, d, L, lists, ws, s);
     return hipGetLastError();
   }
   // the tile sort runs inside each view on the bits of its tile index (at
