@@ -226,6 +226,25 @@ int max_tiles_of(const gs_camera* h, int V) {
 
 }  // namespace
 
+namespace {
+// Waits for words that the device sets in host memory to say that a result is
+// there; after a millisecond without, for the stream.  A wait for an event
+// behind the kernel that writes came back 35 us later, and one for the stream
+// waits for what was enqueued since as well (the cull of 300 k Gaussians and
+// the gather behind it: 49.9 us, 44.6 with the words).
+hipError_t wait_words(const uint32_t* word, int count, hipStream_t s) {
+  const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+  do {
+    for (int k = 0; k < 32; ++k) {
+      while (count > 0 && __atomic_load_n(word + count - 1, __ATOMIC_ACQUIRE) != 0) --count;
+      if (count == 0) return hipSuccess;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() < end);
+  return hipStreamSynchronize(s);
+}
+}  // namespace
+
 extern "C" {
 
 int gs_version(void) { return 100; }
@@ -247,7 +266,8 @@ gs_status gs_create(gs_ctx** out, int device) {
   int prev = 0;
   hipGetDevice(&prev);
   hipSetDevice(device);
-  e = hipHostMalloc(reinterpret_cast<void**>(&c->pinned), 64, hipHostMallocDefault);
+  e = hipHostMalloc(reinterpret_cast<void**>(&c->pinned), 4 * gs::kStatWords,
+                    hipHostMallocDefault);
   if (e != hipSuccess) {
     hipSetDevice(prev);
     delete c;
@@ -400,19 +420,6 @@ static gs_status check_ws_align(gs_ctx* c, const void* ws) {
   return GS_OK;
 }
 
-// Waits up to a millisecond for a word that the device sets in host memory.
-// A wait for an event behind the same kernel came back 35 us later.
-static bool wait_flag(const uint32_t* flag) {
-  const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
-  do {
-    for (int k = 0; k < 32; ++k) {
-      if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != 0) return true;
-      __builtin_ia32_pause();
-    }
-  } while (std::chrono::steady_clock::now() < end);
-  return false;
-}
-
 gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
                       const gs_camera* cd, int V, gs_tile_lists* lists, void* ws, size_t ws_bytes,
                       void* stream) {
@@ -442,7 +449,7 @@ gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
   lists->n_segments = nseg;
   // the kernels write the totals into the context's pinned slot
   uint32_t* stats = c->pinned;
-  for (int k = 0; k < 8; ++k) stats[k] = 0;
+  for (int k = 0; k < gs::kStatWords; ++k) stats[k] = 0;
   hipError_t e = hipSuccess;
   if (proj->n > 0) {
     e = gs::bin_sort_stage1(plan, *proj, cd, ws, stats, s);
@@ -451,10 +458,9 @@ gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
     bool ahead = false;
     e = gs::bin_sort_ahead(plan, *proj, *lists, ws, &ahead, s);
     if (e != hipSuccess) return hip_fail(c, e, "bin_sort (fill)");
-    if (!ahead || !wait_flag(stats + gs::kCountsReady)) {
-      e = hipStreamSynchronize(s);
-      if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
-    }
+    e = ahead ? wait_words(stats + gs::kCountsReady, 1, s)
+              : wait_words(stats + gs::kTotalsReady, 3, s);
+    if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
   }
   const uint64_t M = (uint64_t)stats[2] | ((uint64_t)stats[3] << 32);
   lists->count = (int64_t)M;
@@ -808,11 +814,12 @@ gs_status gs_cull_low_opacity(gs_ctx* c, const float* logit, int n, float min_op
   GS_TRY(use_device(c));
   hipStream_t s = (hipStream_t)stream;
   // the last kernel writes the count into the context's pinned slot
-  *c->pinned = 0;
+  c->pinned[0] = 0;
+  c->pinned[1] = n == 0;
   gs::launch_keep_low_opacity(logit, n, gs::opacity_logit_threshold(min_opacity), kept_index, ws,
                               c->pinned, s);
   GS_LAUNCHED(c, "cull_low_opacity");
-  const hipError_t e = hipStreamSynchronize(s);
+  const hipError_t e = wait_words(c->pinned + 1, 1, s);
   if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
   *kept_host = (int32_t)*c->pinned;
   return GS_OK;

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(1024) void k_keep_scan(uint32_t* __restrict__ count
 }
 
 // SUM: offsets holds the chunk counts, else their scan.  The last workgroup
-// stores the number kept.
+// tells the host the number kept.
 template <bool SUM>
 __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ logit, int n,
                                                     double thr,
@@ -101,7 +101,10 @@ __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ lo
     if (f[k]) index[pre + (uint32_t)__popcll(b & below)] = base + k * 256 + threadIdx.x;
     for (int w = 0; w < 4; ++w) run += s_cnt[k * 4 + w];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = run;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    total[0] = run;
+    tell_host(total + 1);
+  }
 }
 
 // Planes per thread of the gather: their loads are in flight together, and

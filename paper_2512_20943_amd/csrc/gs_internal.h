@@ -104,9 +104,15 @@ size_t bin_sort_workspace_bytes(int n_views, int ld, int64_t capacity, int64_t n
 // written.
 hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
                            const gs_camera* cams_dev, void* ws, uint32_t* stats, hipStream_t s);
-// The word of stats that the direct route's scan sets (system scope) once
-// all the others are written.
-constexpr int kCountsReady = 7;
+// Words of the pinned stats by which the device tells the host what it has
+// written there: kCountsReady, by the direct route's scan, all of them;
+// kTotalsReady + 0, 1 and 2, by the end of stage 1, stats[0..3], [4] and [5].
+constexpr int kStatWords = 16;
+constexpr int kCountsReady = 7, kTotalsReady = 8;
+__device__ __forceinline__ void tell_host(uint32_t* word) {
+  __threadfence_system();
+  __hip_atomic_store(word, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 hipError_t bin_sort_ahead(const BinSortPlan& p, const gs_projected& proj,
                           const gs_tile_lists& lists, void* ws, bool* ahead, hipStream_t s);
 hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const uint32_t* stats,
@@ -143,6 +149,7 @@ void launch_l1(const float* image, const float* target, int64_t count, float* gr
 // low-opacity culling and plane gathers
 size_t keep_workspace_bytes(int n);
 double opacity_logit_threshold(float min_opacity);
+// total: two words of host memory, the number kept and then 1.
 void launch_keep_low_opacity(const float* logit, int n, double thr, int32_t* index, void* ws,
                              uint32_t* total, hipStream_t s);
 void launch_gather(const float* src, int64_t src_ld, int planes, const int32_t* index, int m,

@@ -643,22 +643,24 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t* __restrict__ su
 // into stats[0..3], blocks 1 and 2 scan the visible-pair and instance
 // counts per chunk (totals to stats[4] and stats[5]), block 3 lays out the
 // views' tiles.  stats is the context's pinned host memory: the totals need
-// no copy of their own.
+// no copy of their own, and each of the three blocks says when its own are
+// there (kTotalsReady).
 __global__ __launch_bounds__(kBlock) void k_stage1_close(
     const uint4* __restrict__ part, uint32_t* __restrict__ vis, uint32_t* __restrict__ icnt,
     uint32_t nchunk, uint32_t* __restrict__ stats, const gs_camera* __restrict__ cams, int V,
     uint32_t* __restrict__ seg_base, int32_t* __restrict__ txv) {
-  if (blockIdx.x == 0) {
-    stats_reduce(part, (int)nchunk, stats);
-    return;
-  }
   if (blockIdx.x == 3) {
     view_info(cams, V, seg_base, txv);
     return;
   }
-  uint32_t* a = blockIdx.x == 1 ? vis : icnt;
-  const uint32_t t = block_scan_inplace<64>(a, nchunk);
-  if (threadIdx.x == 0) stats[3 + blockIdx.x] = t;
+  if (blockIdx.x == 0) {
+    stats_reduce(part, (int)nchunk, stats);
+  } else {
+    uint32_t* a = blockIdx.x == 1 ? vis : icnt;
+    const uint32_t t = block_scan_inplace<64>(a, nchunk);
+    if (threadIdx.x == 0) stats[3 + blockIdx.x] = t;
+  }
+  if (threadIdx.x == 0) tell_host(stats + kTotalsReady + blockIdx.x);
 }
 
 // What the emission of one (view, Gaussian) pair needs: its first tile in
@@ -1055,8 +1057,7 @@ __global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__
     counts[nseg] = carry;
     *longest = most;
     *go = all <= capacity && most <= kDirectLongest ? 1u : 0u;
-    __threadfence_system();
-    __hip_atomic_store(ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    tell_host(ready);
   }
 }
 
