@@ -2,9 +2,10 @@
 // in Sec. II; every training view and every delivered view runs it).
 //
 // Large launches: one 64-lane wave (one workgroup) per 16x16 tile; smaller
-// ones: four waves per tile, one per 8x8 quadrant (see the quadrant kernels).
-// With one wave per tile, lane l owns pixel
-// (l & 7, l >> 3) of each of the tile's four 8x8 quadrants ("slots"), so a
+// ones: four waves per tile, one per 8x8 quadrant; the smallest: eight, two
+// per quadrant (see the kernels of those names).  With one wave per tile, lane
+// l owns pixel (l & 7, l >> 3) of each of the tile's four 8x8 quadrants
+// ("slots"), so a
 // slot is a compact 64-pixel block.  The tile's instance list is walked in
 // batches staged in LDS (the forward one record per lane, the backward one
 // per two lanes).  While staging a record, its lane also tests the
@@ -1306,10 +1307,10 @@ __global__ __launch_bounds__(64) void k_render_bwd(
 // ---------------------------------------------------------------- backward,
 // one wave per quadrant
 // The backward for launches with few tiles: a tile is a workgroup of four
-// waves, one per quadrant, which walk the same batches of 64 entries back to front, each over the packed entries its own
-// quadrant needs, four at a time (their alphas, reciprocals and colour
-// products are independent; the transmittance and the colour behind are
-// serial).  A wave sums the four entries' nine values over its 64 pixels
+// waves, one per quadrant, which walk the same batches of 64 entries back to
+// front, each over the packed entries its own quadrant needs, four at a time
+// (their alphas, reciprocals and colour products are independent; the
+// transmittance and the colour behind are serial).  A wave sums the four entries' nine values over its 64 pixels
 // together and stores them; after the batch's one barrier the wave whose
 // turn it is adds the quadrants' sums and writes the rows, while the others
 // go on with the next batch into the other buffer.

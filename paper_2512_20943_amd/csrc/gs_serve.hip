@@ -11,11 +11,11 @@
 // frame group into consecutive view slots, one joint binning over all
 // requests, and one compositing launch over all (request, tile) pairs,
 // straight into the requests' image buffers (a batch of one takes the
-// single-view compositing call, the same image bit for bit).  While arrivals are sparse, a lone request on an
-// idle server is rendered on the scheduler's thread by a renderer of its
-// own, which saves the wake-up of a worker thread.  The plain mode serves
-// the same requests one at a time in arrival order on that renderer: the
-// one-request-per-launch comparison.
+// single-view compositing call, the same image bit for bit).  While arrivals
+// are sparse, a lone request on an idle server is rendered on the scheduler's
+// thread by a renderer of its own, which saves the wake-up of a worker
+// thread.  The plain mode serves the same requests one at a time in arrival
+// order on that renderer: the one-request-per-launch comparison.
 #include <algorithm>
 #include <chrono>
 #include <cmath>

@@ -3,8 +3,9 @@
 // The order the renderer needs is, per tile segment, the instances sorted by
 // (FP32 depth, Gaussian id).  Jobs of few (view, Gaussian) pairs count and
 // fill the tile lists directly and sort each one in registers (the direct
-// route below, plan_direct).  Large ones reach the order in two sorts that
-// both use the same LDS-resident LSD radix sort (stable, 8- or 9-bit digits; per digit,
+// route below, plan_direct), all of it enqueued before the host has read the
+// counts.  Large ones reach the order in two sorts that both use the same
+// LDS-resident LSD radix sort (stable, 8- or 9-bit digits; per digit,
 // per-partition counts, their scan, then LDS ranking and an LDS-staged
 // scatter with those bases; partitions are laid out XCD by XCD, so each of
 // the 8 L2s sees a contiguous range).  Both sorts run inside views: the
