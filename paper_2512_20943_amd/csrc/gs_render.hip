@@ -1123,9 +1123,9 @@ __global__ __launch_bounds__(64) void k_render_bwd(
     const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
     float bg1, float bg2, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimage, float* __restrict__ rows,
-    unsigned long long* __restrict__ cnt) {
+    unsigned long long* __restrict__ cnt, const uint32_t* __restrict__ order) {
   __shared__ BwdShared sh;
-  const int seg = blockIdx.x;
+  const int seg = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
   const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
   const int ty = tile / TX, tx = tile - ty * TX;
   const int lane = threadIdx.x;
@@ -1360,9 +1360,9 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
     const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
     float bg1, float bg2, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimage, float* __restrict__ rows,
-    unsigned long long* __restrict__ cnt) {
+    unsigned long long* __restrict__ cnt, const uint32_t* __restrict__ order) {
   __shared__ QuadBwdShared sh;
-  const int seg = blockIdx.x;
+  const int seg = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
   const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
   const int ty = tile / TX, tx = tile - ty * TX;
   const int lane = threadIdx.x & 63;
@@ -1545,7 +1545,7 @@ __global__ __launch_bounds__(512) void k_render_bwd_octs(
     const uint2* __restrict__ ranges, int W, int H, int TX, int tiles_per_view, float bg0,
     float bg1, float bg2, const float* __restrict__ final_T, const int32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimage, float* __restrict__ rows,
-    unsigned long long* __restrict__ cnt) {
+    unsigned long long* __restrict__ cnt, const uint32_t* __restrict__) {
   __shared__ OctBwdShared sh;
   const int seg = blockIdx.x;
   const int v = seg / tiles_per_view, tile = seg - v * tiles_per_view;
@@ -1722,6 +1722,38 @@ __global__ __launch_bounds__(512) void k_render_bwd_octs(
   }
 }
 
+// The tiles of a launch, longest list first (by 32 entries, the order of a
+// class is arbitrary), so that the lists that take longest do not start last.
+// One workgroup.
+constexpr int kOrderThreads = 1024, kOrderClasses = 128;
+
+__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2* __restrict__ ranges,
+                                                              int tiles,
+                                                              uint32_t* __restrict__ order) {
+  __shared__ uint32_t at[kOrderClasses];
+  auto class_of = [&](int t) {
+    const uint2 r = ranges[t];
+    return kOrderClasses - 1 - (int)min((r.y - r.x + 31) / 32, (uint32_t)kOrderClasses - 1);
+  };
+  for (int c = threadIdx.x; c < kOrderClasses; c += kOrderThreads) at[c] = 0;
+  __syncthreads();
+  for (int t = threadIdx.x; t < tiles; t += kOrderThreads) atomicAdd(&at[class_of(t)], 1u);
+  __syncthreads();
+  if (threadIdx.x < 64) {  // exclusive scan of the classes, two per lane
+    const uint32_t a = at[2 * threadIdx.x], b = at[2 * threadIdx.x + 1];
+    uint32_t x = a + b;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(x, off, 64);
+      if ((int)threadIdx.x >= off) x += y;
+    }
+    at[2 * threadIdx.x] = x - a - b;
+    at[2 * threadIdx.x + 1] = x - b;
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < tiles; t += kOrderThreads)
+    order[atomicAdd(&at[class_of(t)], 1u)] = (uint32_t)t;
+}
+
 // One step of a segmented inclusive scan of nine values over the wave: add
 // the value of the lane CTRL names when it carries the same pair index q.
 // q does not decrease over the lanes, so equal ends mean that every lane in
@@ -1851,6 +1883,13 @@ constexpr int kOctTiles = 640;
 // tiles 60.1 -> 58.3 us, 3,813 tiles 54.0 -> 50.9, 7,752 tiles 125.3 -> 123.7,
 // 32,640 tiles 550 -> 560.
 constexpr int kL1OneTiles = 8192;
+// Most tiles of a backward launch that starts with its longest lists (beyond,
+// the last round of waves is a small part of the launch, and neighbouring
+// tiles share records in the L2s).  render_bwd with the ordering's launch, in
+// launch order -> longest first, in us: 1,200 tiles (0.65 M instances) 165 ->
+// 156, 3,813 tiles 128 -> 105, 7,752 tiles 301 -> 260, 16,320 tiles 562 -> 555,
+// 32,640 tiles 1,031 -> 1,016, 54,400 tiles 1,620 -> 1,649.
+constexpr int kOrderTiles = 36000;
 }  // namespace
 
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
@@ -1972,13 +2011,21 @@ void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int
   {
     StageScope scope(kStRenderBwd, s);
     const bool octs = blocks <= kOctTiles, quads = blocks <= kQuadBwdTiles;
+    // the order lies in grad2d, which is written after this launch
+    uint32_t* order = nullptr;
+    if (!octs && blocks <= kOrderTiles &&
+        (size_t)blocks <= (size_t)kGrad2dFloats * proj.ld * (size_t)V) {
+      order = reinterpret_cast<uint32_t*>(grad2d);
+      hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(kOrderThreads), 0, s,
+                         reinterpret_cast<const uint2*>(lists.ranges), blocks, order);
+    }
     auto kernel = octs    ? (g_work ? k_render_bwd_octs<true> : k_render_bwd_octs<false>)
                   : quads ? (g_work ? k_render_bwd_quads<true> : k_render_bwd_quads<false>)
                           : (g_work ? k_render_bwd<true> : k_render_bwd<false>);
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(octs ? 512 : quads ? 256 : 64), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
-                       bg[2], final_T, n_contrib, dL_dimage, rows, g_work);
+                       bg[2], final_T, n_contrib, dL_dimage, rows, g_work, order);
   }
   const size_t nv = (size_t)proj.n * (size_t)V;
   if (nv == 0) return;

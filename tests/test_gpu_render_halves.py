@@ -97,3 +97,30 @@ def test_l1_sum_over_tiles(views, k):
     want = 0.5 + float((out["image"] - target).abs().double().mean())
     # FP64 sums of the same FP32 differences
     assert abs(float(loss) - want) <= 1e-12
+
+
+@pytest.mark.parametrize("w,h", [(1920, 1080), (640, 480)])
+def test_backward_with_and_without_an_order_of_tiles(w, h):
+    """48 splats in 8,160 and 1,200 tiles: the gradient records of 64 columns
+    are too small for the tiles' order, those of 4,096 (the rest behind the
+    camera) hold it.  The same rows either way, so the same bits."""
+    require_gpu()
+    print(f"order {w}x{h}", flush=True)
+    scene = scenes.make_scene(48, 2, -1.0, 1.0, -1.5, 0.6, 1)
+    more = scenes.make_scene(4_000, 3, -1.0, 1.0, -4.0, 0.5, 1)
+    more["mean"][2, :4_000] = -50.0
+    for k in ("mean", "log_scale", "quat", "opacity", "sh"):
+        more[k][..., :48] = scene[k][..., :48]
+    cams = gs.Cameras(scenes.axis_camera(w, h, 4.0))
+    dimg = torch.rand(1, 3, h, w, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+
+    def grads(sc):
+        g = gs.Gaussians.from_scene(sc)
+        r = Rasterizer(ctx=gs.Context(torch.cuda.current_device()), capacity=1 << 20)
+        out = r.forward(g, cams, BG)
+        grad = gs.Gaussians.zeros_like(g)
+        r.backward(g, cams, out, dimg, grad, BG)
+        return [p[..., :48].clone() for p in grad.planes()]
+
+    for a, b in zip(grads(scene), grads(more)):
+        assert a.abs().max() > 0 and torch.equal(a, b)
