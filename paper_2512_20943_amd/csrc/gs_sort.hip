@@ -658,7 +658,9 @@ __global__ __launch_bounds__(kBlock) void k_stage1_close(
     stats_reduce(part, (int)nchunk, stats);
   } else {
     uint32_t* a = blockIdx.x == 1 ? vis : icnt;
-    const uint32_t t = block_scan_inplace<64>(a, nchunk);
+    // 64 values per thread and round, or 4 where one round of them is enough
+    const uint32_t t = nchunk <= 4 * kBlock ? block_scan_inplace<4>(a, nchunk)
+                                            : block_scan_inplace<64>(a, nchunk);
     if (threadIdx.x == 0) stats[3 + blockIdx.x] = t;
   }
   if (threadIdx.x == 0) tell_host(stats + kTotalsReady + blockIdx.x);
@@ -961,7 +963,11 @@ __global__ __launch_bounds__(kChunkThreads) void k_tile_count(
 
 // Exclusive scan of each tile's column of rows over the view's chunks, in
 // place; the column total to counts[seg].  A workgroup takes 64 tiles, its
-// 16 waves a sixteenth of the chunks each.
+// 16 waves a sixteenth of the chunks each, kColumnRows of them with their
+// loads in flight together (and only once where a wave has no more): 147
+// chunks of 3,600 tiles 6.9 -> 5.0 us.
+constexpr uint32_t kColumnRows = 16;
+
 __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uint32_t chunks,
                                                        const uint32_t* __restrict__ seg_base,
                                                        uint32_t* __restrict__ rows,
@@ -972,7 +978,12 @@ __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uin
   const uint32_t per = (chunks + 15) / 16;
   const uint32_t k0 = min((uint32_t)wave * per, chunks), k1 = min(k0 + per, chunks);
   uint32_t* col = nullptr;
-  uint32_t nt = 0, sum = 0;
+  uint32_t nt = 0, sum = 0, x[kColumnRows];
+  auto load = [&](uint32_t kb) {
+#pragma unroll
+    for (uint32_t u = 0; u < kColumnRows; ++u)
+      x[u] = kb + u < k1 ? col[(size_t)(kb + u) * nt] : 0u;
+  };
   if (seg < nseg) {
     int lo = 0, hi = V - 1;  // last view whose base <= seg
     while (lo < hi) {
@@ -982,7 +993,11 @@ __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uin
     const uint32_t sb = seg_base[lo];
     nt = seg_base[lo + 1] - sb;
     col = rows + (size_t)chunks * sb + (seg - sb);
-    for (uint32_t k = k0; k < k1; ++k) sum += col[(size_t)k * nt];
+    for (uint32_t kb = k0; kb < k1; kb += kColumnRows) {
+      load(kb);
+#pragma unroll
+      for (uint32_t u = 0; u < kColumnRows; ++u) sum += x[u];
+    }
   }
   s_sum[wave][lane] = sum;
   __syncthreads();
@@ -992,10 +1007,13 @@ __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uin
     total += s_sum[w][lane];
   }
   if (seg < nseg) {
-    for (uint32_t k = k0; k < k1; ++k) {
-      const uint32_t x = col[(size_t)k * nt];
-      col[(size_t)k * nt] = run;
-      run += x;
+    for (uint32_t kb = k0; kb < k1; kb += kColumnRows) {
+      if (per > kColumnRows) load(kb);
+#pragma unroll
+      for (uint32_t u = 0; u < kColumnRows; ++u) {
+        if (kb + u < k1) col[(size_t)(kb + u) * nt] = run;
+        run += x[u];
+      }
     }
     if (wave == 0) counts[seg] = total;
   }

@@ -80,3 +80,19 @@ def test_capacity(middle, short_by):
         np.testing.assert_array_equal(vals[:M].cpu().numpy().view(np.uint32), L_or["vals"])
         np.testing.assert_array_equal(ranges.cpu().numpy().view(np.uint32).reshape(-1, 2),
                                       L_or["ranges"])
+
+
+# a wave's share of a tile's column: 1 chunk of 2,048 Gaussians, 16, 17 and 33
+@pytest.mark.parametrize("n", [2_000, 16 * 16 * 2048, 16 * 16 * 2048 + 1, 33 * 16 * 2048])
+def test_columns_of_many_chunks(n):
+    require_gpu()
+    print(f"columns of {n} Gaussians", flush=True)
+    scene = scenes.make_scene(n, 6, -1.0, 1.0, -6.5, 0.3, 0)
+    cams = scenes.arc_cameras(1, 4.0, 1040, 1000)
+    _, _, _, out = gpu_forward(scene, cams, capacity=1 << 23, tight_rect=True, tile_spans=True)
+    L_or = oracle.bin_sort(oracle.project(scene, cams, "spans"), cams)
+    L_g = lists_to_numpy(out["lists"])
+    assert L_g["count"] == L_or["count"] > n // 2
+    assert np.diff(L_or["ranges"].astype(np.int64), axis=1).max() <= 4096
+    for k in ("vals", "ranges"):
+        np.testing.assert_array_equal(L_g[k], L_or[k], err_msg=k)
