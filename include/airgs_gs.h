@@ -559,9 +559,10 @@ gs_status gs_usage_masks(gs_ctx* ctx, const uint32_t* usage, int n, int gw, int 
  * threshold are discarded during keyframe training).  Gaussian i < n is kept
  * iff sigmoid(opacity_logit[i]) >= min_opacity, decided as logit >=
  * log(m / (1 - m)) in FP64.  WRITES the kept indices in increasing order to
- * kept_index (device, capacity n) and their number to *kept_host; blocks
- * until the count has been read back.  workspace: gs_cull_workspace_size(n)
- * bytes.  min_opacity must lie in (0, 1). */
+ * kept_index (device, capacity n) and their number to *kept_host; waits for
+ * the stream, so both are complete at return and the workspace is free.
+ * workspace: gs_cull_workspace_size(n) bytes.  min_opacity must lie in
+ * (0, 1). */
 size_t gs_cull_workspace_size(int n);
 gs_status gs_cull_low_opacity(gs_ctx* ctx, const float* opacity_logit, int n, float min_opacity,
                               int32_t* kept_index, int32_t* kept_host, void* workspace,

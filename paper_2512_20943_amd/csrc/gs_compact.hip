@@ -63,7 +63,8 @@ __global__ __launch_bounds__(1024) void k_keep_scan(uint32_t* __restrict__ count
 }
 
 // SUM: offsets holds the chunk counts, else their scan.  The last workgroup
-// tells the host the number kept.
+// writes the number kept to host memory, for a host that waits for the stream:
+// the other workgroups may still be reading the counts and writing indices.
 template <bool SUM>
 __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ logit, int n,
                                                     double thr,
@@ -101,10 +102,7 @@ __global__ __launch_bounds__(256) void k_keep_write(const float* __restrict__ lo
     if (f[k]) index[pre + (uint32_t)__popcll(b & below)] = base + k * 256 + threadIdx.x;
     for (int w = 0; w < 4; ++w) run += s_cnt[k * 4 + w];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    total[0] = run;
-    tell_host(total + 1);
-  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = run;
 }
 
 // Planes per thread of the gather: their loads are in flight together, and

@@ -149,7 +149,7 @@ void launch_l1(const float* image, const float* target, int64_t count, float* gr
 // low-opacity culling and plane gathers
 size_t keep_workspace_bytes(int n);
 double opacity_logit_threshold(float min_opacity);
-// total: two words of host memory, the number kept and then 1.
+// total: a word of host memory for the number kept, not written when n is 0.
 void launch_keep_low_opacity(const float* logit, int n, double thr, int32_t* index, void* ws,
                              uint32_t* total, hipStream_t s);
 void launch_gather(const float* src, int64_t src_ld, int planes, const int32_t* index, int m,

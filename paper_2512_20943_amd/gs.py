@@ -654,7 +654,7 @@ def gs_usage_masks(ctx: Context, usage, n: int, gw: int, gh: int, drops, masks, 
 def gs_cull_low_opacity(ctx: Context, opacity_logit, n: int, min_opacity: float, kept_index,
                         workspace=None, stream=None) -> int:
     """Indices of the Gaussians kept by low-opacity culling (written to
-    ``kept_index``); returns their number (blocking)."""
+    ``kept_index``); returns their number once the indices are complete."""
     if workspace is None:
         workspace = torch.empty(max(cull_workspace_size(n), 1), dtype=torch.uint8,
                                 device=opacity_logit.device)
