@@ -231,12 +231,12 @@ namespace {
 // there; after a millisecond without, for the stream.  A wait for an event
 // behind the kernel that writes came back 35 us later, and one for the stream
 // waits for what was enqueued since as well.
-hipError_t wait_words(const uint32_t* word, int count, hipStream_t s) {
+template <typename Ready>
+hipError_t wait_words(Ready ready, hipStream_t s) {
   const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
   do {
     for (int k = 0; k < 32; ++k) {
-      while (count > 0 && __atomic_load_n(word + count - 1, __ATOMIC_ACQUIRE) != 0) --count;
-      if (count == 0) return hipSuccess;
+      if (ready()) return hipSuccess;
       __builtin_ia32_pause();
     }
   } while (std::chrono::steady_clock::now() < end);
@@ -457,9 +457,16 @@ gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
     bool ahead = false;
     e = gs::bin_sort_ahead(plan, *proj, *lists, ws, &ahead, s);
     if (e != hipSuccess) return hip_fail(c, e, "bin_sort (fill)");
-    e = ahead ? wait_words(stats + gs::kCountsReady, 1, s)
-              : wait_words(stats + gs::kTotalsReady, 3, s);
+    auto told = [&](int k) { return __atomic_load_n(stats + k, __ATOMIC_ACQUIRE) != 0; };
+    auto by_radix = [&] { return !ahead || told(gs::kCrowded); };
+    e = wait_words(
+        [&] {
+          constexpr int k = gs::kTotalsReady;
+          return by_radix() ? told(k) && told(k + 1) && told(k + 2) : told(gs::kCountsReady);
+        },
+        s);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+    if (by_radix()) stats[gs::kLongest] = UINT32_MAX;  // not counted
   }
   const uint64_t M = (uint64_t)stats[2] | ((uint64_t)stats[3] << 32);
   lists->count = (int64_t)M;

@@ -106,9 +106,12 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
                            const gs_camera* cams_dev, void* ws, uint32_t* stats, hipStream_t s);
 // Words of the pinned stats by which the device tells the host what it has
 // written there: kCountsReady, by the direct route's scan, all of them;
-// kTotalsReady + 0, 1 and 2, by the end of stage 1, stats[0..3], [4] and [5].
+// kTotalsReady + 0, 1 and 2, by the end of stage 1, stats[0..3], [4] and [5];
+// kCrowded, by the end of stage 1 too, that a list is taken to be too long for
+// the direct route, whose kernels then do nothing and tell nothing.  A call
+// returns only when nothing of it will write to a word any more.
 constexpr int kStatWords = 16;
-constexpr int kCountsReady = 7, kTotalsReady = 8;
+constexpr int kLongest = 6, kCountsReady = 7, kTotalsReady = 8, kCrowded = 11;
 __device__ __forceinline__ void tell_host(uint32_t* word) {
   __threadfence_system();
   __hip_atomic_store(word, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

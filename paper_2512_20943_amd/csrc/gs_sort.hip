@@ -27,6 +27,7 @@
 // ceil(log2(tiles per view)/9) digits of 32-bit keys instead of 5-7 digits
 // of 64-bit keys.
 #include <algorithm>
+#include <cmath>
 
 #include "gs_internal.h"
 
@@ -431,20 +432,156 @@ __device__ __forceinline__ void grid_zero(uint32_t* __restrict__ zero, size_t ze
     zero[z] = 0u;
 }
 
+// What the emission of one (view, Gaussian) pair needs: its first tile in
+// the view, id, rectangle width | kSpanFlag, and the per-row spans or the
+// bits of 1 / width.
+__device__ __forceinline__ uint4 emit_entry(const uint32_t* __restrict__ record_tail, uint32_t id,
+                                            uint32_t tiles_per_row) {
+  const uint2 ow = *reinterpret_cast<const uint2*>(record_tail);  // origin, width | flag
+  const uint32_t spans = record_tail[3];
+  return make_uint4((ow.x >> 16) * tiles_per_row + (ow.x & 0xFFFFu), id, ow.y,
+                    ow.y & kSpanFlag ? spans : __float_as_uint(1.f / (float)ow.y));
+}
+
+// Tile (in the view) of the pair's instance l: row by row over its spans or
+// its rectangle.
+__device__ __forceinline__ uint32_t entry_tile(const uint4& en, uint32_t tiles_per_row,
+                                               uint32_t l) {
+  uint32_t dy, dx;
+  if (en.z & kSpanFlag) {
+    // spans s_r = b_r - a_r per byte; instances before row r: p_r
+    const uint32_t m = en.w;
+    const uint32_t sp = ((m >> 4) & 0x0F0F0F0Fu) - (m & 0x0F0F0F0Fu);
+    const uint32_t p1 = sp & 0xFFu, p2 = p1 + ((sp >> 8) & 0xFFu), p3 = p2 + ((sp >> 16) & 0xFFu);
+    dy = (uint32_t)(l >= p1) + (uint32_t)(l >= p2) + (uint32_t)(l >= p3);
+    const uint32_t before = dy == 0 ? 0u : (dy == 1 ? p1 : (dy == 2 ? p2 : p3));
+    dx = ((m >> (8 * dy)) & 15u) + (l - before);
+  } else {
+    // l / width: a rectangle has at most 2^24 tiles, so the float quotient
+    // is off by at most one
+    dy = (uint32_t)((float)l * __uint_as_float(en.w));
+    int32_t r = (int32_t)(l - dy * en.z);
+    if (r < 0) {
+      --dy;
+      r += (int32_t)en.z;
+    } else if (r >= (int32_t)en.z) {
+      ++dy;
+      r -= (int32_t)en.z;
+    }
+    dx = (uint32_t)r;
+  }
+  return en.x + dy * tiles_per_row + dx;
+}
+
+constexpr int kChunkTiles = 8192;  // most tiles of a view of the direct route: its LDS counters
+constexpr uint32_t kDirectLongest = 4096;  // keys a sorting workgroup holds
+
+// A sample of each view's Gaussians that tells, before the direct route spends
+// anything on a job, whether some tile's list will be too long for its sort:
+// then the job belongs to the radix sorts.  Two parts, each beside the work of
+// a launch that is there anyway: the sampled pairs' tiles are written out, and
+// added up per tile.  gs_bin_sort of crowded jobs in us, all instances counted
+// before the route is left / with the sample / radix sorts from the start on:
+// 60 k Gaussians at 64x64 135 / 125 / 120, 300 k in a few tiles of 1280x720
+// 184 / 170 / 163, 1 M 246 / 220 / 207, 2 M 376 / 319 / 305 (what is left are
+// the direct route's launches, which do nothing).  Jobs that stay pay 2-3 us.
+// One pair in 64 because a list of 4,097 then has 64 +- 8 pairs in the sample;
+// counters of all XCDs in memory in place of one workgroup's took 25-100 us.
+constexpr uint32_t kSampleEvery = 64;     // of all views together one pair in as many,
+constexpr uint32_t kSampleLeast = 2048, kSampleMost = 16384;  // within these
+constexpr uint32_t kSampleWeight = 7;     // most tiles that one of a pair's two stands for
+static_assert(kChunkTiles <= 1 << 13, "13 bits per tile of a sampled pair");
+
+struct CrowdSample {
+  uint32_t* tiles;    // per sampled pair: two tiles of 13 bits, their number (2 bits), weight
+  uint32_t* crowded;  // device flag
+  uint32_t views, per_view;
+  uint32_t stride;      // Gaussians per sampled one
+  uint32_t view_tiles;  // most tiles of a view
+  uint32_t limit;       // weighted pairs of one tile from which on it is crowded
+};
+
+// Sample k: one Gaussian of stratum k % per_view of view k / per_view, and one
+// or two of its tiles, at a random offset.
+__device__ __forceinline__ void crowd_sample(const CrowdSample& cs, uint32_t k, int ld,
+                                             const gs_camera* __restrict__ cams,
+                                             const int32_t* __restrict__ tiles,
+                                             const uint32_t* __restrict__ splat_words) {
+  if (k >= cs.views * cs.per_view) return;
+  const uint32_t v = k / cs.per_view, j = k - v * cs.per_view;
+  const uint32_t h = k * 2654435761u;
+  const uint32_t i = j * cs.stride + __umulhi(h, cs.stride);
+  const size_t at = (size_t)v * ld + i;
+  const uint32_t tx = (uint32_t)tiles_across(cams[v].width);
+  const uint4 en = emit_entry(splat_words + at * (4 * kSplatF4) + 12, i, tx);
+  const uint32_t nt = (uint32_t)max(tiles[at], 0);
+  uint32_t out = 0;
+  if (nt > 0) {
+    const uint32_t l0 = __umulhi(h * 747796405u, nt), l = l0 + nt / 2;
+    out = entry_tile(en, tx, l0) & (kChunkTiles - 1);
+    out |= (entry_tile(en, tx, l < nt ? l : l - nt) & (kChunkTiles - 1)) << 13;
+    out |= min(nt, 2u) << 26 | min(max(nt / 2, 1u), kSampleWeight) << 28;
+  }
+  cs.tiles[k] = out;
+}
+
+// One workgroup adds up view v's sample.  The one thread that raises the flag
+// tells the host, so nothing else of the call writes that word.
+__device__ __forceinline__ void crowd_count(const CrowdSample& cs, uint32_t v,
+                                            uint32_t* __restrict__ crowded_host) {
+  __shared__ uint32_t s_count[kChunkTiles];
+  const uint32_t* mine = cs.tiles + (size_t)v * cs.per_view;
+  constexpr uint32_t kAhead = 24;
+  uint32_t x[kAhead];
+  auto load = [&](uint32_t j0) {
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u)
+      x[u] = j0 + u * kBlock < cs.per_view ? mine[j0 + u * kBlock] : 0;
+  };
+  load(threadIdx.x);
+  for (uint32_t t = threadIdx.x; t < cs.view_tiles; t += kBlock) s_count[t] = 0u;
+  __syncthreads();
+  for (uint32_t j0 = threadIdx.x; j0 < cs.per_view;) {
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      const uint32_t m = (x[u] >> 26) & 3u, w = x[u] >> 28;
+      if (m > 0) atomicAdd(&s_count[x[u] & (kChunkTiles - 1)], w);
+      if (m > 1) atomicAdd(&s_count[(x[u] >> 13) & (kChunkTiles - 1)], w);
+    }
+    j0 += kAhead * kBlock;
+    load(j0);
+  }
+  __syncthreads();
+  uint32_t most = 0;
+  for (uint32_t t = threadIdx.x; t < cs.view_tiles; t += kBlock) most = max(most, s_count[t]);
+  if (__syncthreads_or(most >= cs.limit) && threadIdx.x == 0 && atomicExch(cs.crowded, 1u) == 0)
+    tell_host(crowded_host);
+}
+
 // Per chunk of kCountChunk Gaussians of one view (grid x; views on grid y,
-// looping past 65535 of them), chunk c = v * gridDim.x + blockIdx.x: the
+// looping past 65535 of them), chunk c = v * gx + blockIdx.x: the
 // range of the depth bits of its visible pairs and their instance count,
 // part[c] = {min bits, max bits, count lo, count hi}, the number of its
 // visible pairs, vis[c], and the count's low word again, icnt[c] (scanned,
 // it places each view's instances).  Thread t owns Gaussians 8t .. 8t + 7.
+// Workgroups past the chunks' gx columns take the sample.
 __global__ __launch_bounds__(kBlock) void k_depth_range(int n, int ld, int V,
                                                         const uint32_t* __restrict__ depth_bits,
                                                         const int32_t* __restrict__ tiles,
                                                         uint4* __restrict__ part,
                                                         uint32_t* __restrict__ vis,
-                                                        uint32_t* __restrict__ icnt) {
+                                                        uint32_t* __restrict__ icnt,
+                                                        uint32_t gx, CrowdSample cs,
+                                                        const gs_camera* __restrict__ cams,
+                                                        const uint32_t* __restrict__ splat_words) {
   __shared__ uint32_t s_min[4], s_max[4], s_cnt[4];
   __shared__ unsigned long long s_sum[4];
+  if (blockIdx.x >= gx) {
+    const uint32_t b = (blockIdx.x - gx) * gridDim.y + blockIdx.y;
+    crowd_sample(cs, b * kBlock + threadIdx.x, ld, cams, tiles, splat_words);
+    return;
+  }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *cs.crowded = 0u;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool vec = rows_aligned(ld, tiles, depth_bits);
   for (int v = blockIdx.y; v < V; v += gridDim.y) {
@@ -481,7 +618,7 @@ __global__ __launch_bounds__(kBlock) void k_depth_range(int n, int ld, int V,
       mn = min(min(s_min[0], s_min[1]), min(s_min[2], s_min[3]));
       mx = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
       sum = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
-      const size_t c = (size_t)v * gridDim.x + blockIdx.x;
+      const size_t c = (size_t)v * gx + blockIdx.x;
       part[c] = make_uint4(mn, mx, (uint32_t)sum, (uint32_t)(sum >> 32));
       vis[c] = (s_cnt[0] + s_cnt[1]) + (s_cnt[2] + s_cnt[3]);
       icnt[c] = (uint32_t)sum;
@@ -643,13 +780,18 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(uint32_t* __restrict__ su
 // The end of stage 1 in one launch: block 0 reduces the chunk partials
 // into stats[0..3], blocks 1 and 2 scan the visible-pair and instance
 // counts per chunk (totals to stats[4] and stats[5]), block 3 lays out the
-// views' tiles.  stats is the context's pinned host memory: the totals need
-// no copy of their own, and each of the three blocks says when its own are
-// there (kTotalsReady).
+// views' tiles, and the others, where there are some, add up the sample.
+// stats is the context's pinned host memory: the totals need no copy of their
+// own, and each of the first three blocks says when its own are there
+// (kTotalsReady).
 __global__ __launch_bounds__(kBlock) void k_stage1_close(
     const uint4* __restrict__ part, uint32_t* __restrict__ vis, uint32_t* __restrict__ icnt,
     uint32_t nchunk, uint32_t* __restrict__ stats, const gs_camera* __restrict__ cams, int V,
-    uint32_t* __restrict__ seg_base, int32_t* __restrict__ txv) {
+    uint32_t* __restrict__ seg_base, int32_t* __restrict__ txv, CrowdSample cs) {
+  if (blockIdx.x > 3) {
+    crowd_count(cs, blockIdx.x - 4, stats + kCrowded);
+    return;
+  }
   if (blockIdx.x == 3) {
     view_info(cams, V, seg_base, txv);
     return;
@@ -664,47 +806,6 @@ __global__ __launch_bounds__(kBlock) void k_stage1_close(
     if (threadIdx.x == 0) stats[3 + blockIdx.x] = t;
   }
   if (threadIdx.x == 0) tell_host(stats + kTotalsReady + blockIdx.x);
-}
-
-// What the emission of one (view, Gaussian) pair needs: its first tile in
-// the view, id, rectangle width | kSpanFlag, and the per-row spans or the
-// bits of 1 / width.
-__device__ __forceinline__ uint4 emit_entry(const uint32_t* __restrict__ record_tail, uint32_t id,
-                                            uint32_t tiles_per_row) {
-  const uint2 ow = *reinterpret_cast<const uint2*>(record_tail);  // origin, width | flag
-  const uint32_t spans = record_tail[3];
-  return make_uint4((ow.x >> 16) * tiles_per_row + (ow.x & 0xFFFFu), id, ow.y,
-                    ow.y & kSpanFlag ? spans : __float_as_uint(1.f / (float)ow.y));
-}
-
-// Tile (in the view) of the pair's instance l: row by row over its spans or
-// its rectangle.
-__device__ __forceinline__ uint32_t entry_tile(const uint4& en, uint32_t tiles_per_row,
-                                               uint32_t l) {
-  uint32_t dy, dx;
-  if (en.z & kSpanFlag) {
-    // spans s_r = b_r - a_r per byte; instances before row r: p_r
-    const uint32_t m = en.w;
-    const uint32_t sp = ((m >> 4) & 0x0F0F0F0Fu) - (m & 0x0F0F0F0Fu);
-    const uint32_t p1 = sp & 0xFFu, p2 = p1 + ((sp >> 8) & 0xFFu), p3 = p2 + ((sp >> 16) & 0xFFu);
-    dy = (uint32_t)(l >= p1) + (uint32_t)(l >= p2) + (uint32_t)(l >= p3);
-    const uint32_t before = dy == 0 ? 0u : (dy == 1 ? p1 : (dy == 2 ? p2 : p3));
-    dx = ((m >> (8 * dy)) & 15u) + (l - before);
-  } else {
-    // l / width: a rectangle has at most 2^24 tiles, so the float quotient
-    // is off by at most one
-    dy = (uint32_t)((float)l * __uint_as_float(en.w));
-    int32_t r = (int32_t)(l - dy * en.z);
-    if (r < 0) {
-      --dy;
-      r += (int32_t)en.z;
-    } else if (r >= (int32_t)en.z) {
-      ++dy;
-      r -= (int32_t)en.z;
-    }
-    dx = (uint32_t)r;
-  }
-  return en.x + dy * tiles_per_row + dx;
 }
 
 // Emit (tile of the view, Gaussian id) for each tile of each depth-sorted
@@ -834,7 +935,6 @@ __global__ __launch_bounds__(kBlock) void k_emit(uint32_t N, int ld, uint32_t vs
 // instead of 22, and two of them, not 17, after the host has read the
 // instance count.
 constexpr int kChunkThreads = 1024;
-constexpr int kChunkTiles = 8192;  // most tiles of a view: the LDS counters
 static_assert(kCountChunk == 2 * kChunkThreads, "two Gaussians per thread");
 
 struct ChunkPairs {  // a chunk's pairs that have instances, in id order
@@ -939,10 +1039,12 @@ __device__ __forceinline__ uint32_t xcd_chunk() {
 }
 
 // rows[chunk of the view][tile]: instances per tile.  Grid: chunks by views.
+// Nothing happens in a crowded job, here and in the two kernels behind.
 __global__ __launch_bounds__(kChunkThreads) void k_tile_count(
     int n, int ld, int V, const int32_t* __restrict__ tiles, uint32_t* __restrict__ splat_words,
     const uint32_t* __restrict__ seg_base, const int32_t* __restrict__ txv,
-    uint32_t* __restrict__ rows) {
+    const uint32_t* __restrict__ crowded, uint32_t* __restrict__ rows) {
+  if (*crowded != 0) return;
   __shared__ ChunkPairs sh;
   const uint32_t chunk = xcd_chunk();
   for (int v = blockIdx.y; v < V; v += gridDim.y) {
@@ -970,8 +1072,10 @@ constexpr uint32_t kColumnRows = 16;
 
 __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uint32_t chunks,
                                                        const uint32_t* __restrict__ seg_base,
+                                                       const uint32_t* __restrict__ crowded,
                                                        uint32_t* __restrict__ rows,
                                                        uint32_t* __restrict__ counts) {
+  if (*crowded != 0) return;
   __shared__ uint32_t s_sum[16][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t seg = blockIdx.x * 64 + lane;
@@ -1024,14 +1128,18 @@ __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uin
 // at most `capacity` instances, no list above kDirectLongest.  The longest
 // list goes to *longest in host memory, and then, when the host may read all
 // that this and the kernels before it wrote there, 1 to *ready.
-constexpr uint32_t kDirectLongest = 4096;  // keys a sorting workgroup holds
 constexpr int kScanBlock = 1024;
 
 __global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__ counts,
                                                           uint32_t nseg, uint64_t capacity,
+                                                          const uint32_t* __restrict__ crowded,
                                                           uint32_t* __restrict__ longest,
                                                           uint32_t* __restrict__ ready,
                                                           uint32_t* __restrict__ go) {
+  if (*crowded != 0) {  // the host knows and does not wait for this
+    if (threadIdx.x == 0) *go = 0u;
+    return;
+  }
   __shared__ uint32_t s_wave[kScanBlock / 64], s_max[kScanBlock / 64];
   constexpr uint32_t kPer = 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1646,6 +1754,14 @@ struct DirectPlan {
 // radix passes write runs.
 constexpr int64_t kDirectPairs = 3000000;
 
+// Sampled pairs of one tile from which on a job counts as crowded, with
+// `sampled` of a view's n Gaussians: those of a list above kDirectLongest,
+// less two standard deviations (none where every Gaussian is sampled).
+uint32_t crowd_limit(uint32_t sampled, uint32_t n) {
+  const double f = (double)sampled / (double)n, mean = f * (kDirectLongest + 1);
+  return std::max(1u, (uint32_t)std::ceil(mean - 2.0 * std::sqrt(mean * (1.0 - f))));
+}
+
 DirectPlan plan_direct(const BinSortPlan& p, const Layout& L) {
   DirectPlan d{};
   const int64_t chunks = cdiv((uint64_t)p.n, kCountChunk);
@@ -1669,28 +1785,47 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
   uint4* part = at<uint4>(ws, L.dparts);
   uint32_t* vis = at<uint32_t>(ws, L.vparts);
   uint32_t* icnt = at<uint32_t>(ws, L.iparts);
-  hipLaunchKernelGGL(k_depth_range, dim3(gx, gy), dim3(kBlock), 0, s, p.n, p.ld, p.n_views,
-                     proj.depth_bits, proj.tiles_touched, part, vis, icnt);
+  const DirectPlan d = plan_direct(p, L);
+  const uint32_t nseg = (uint32_t)p.n_segments;
+  uint32_t* crowded = at<uint32_t>(ws, L.total) + 1;
+  CrowdSample cs{};
+  cs.crowded = crowded;
+  uint32_t sample_blocks = 0;
+  if (d.possible && p.n > (int)kDirectLongest) {  // else no list can be longer
+    // in the place of the rows of counts, which come later: at most 4 of the
+    // 28 bytes that the workspace has per pair up to there
+    cs.tiles = at<uint32_t>(ws, d.rows);
+    cs.views = (uint32_t)p.n_views;
+    const uint32_t pairs = std::min(
+        std::max(cs.views * (uint32_t)p.n / kSampleEvery, kSampleLeast), kSampleMost);
+    cs.stride = cdiv((uint64_t)cs.views * (uint64_t)p.n, pairs);
+    cs.per_view = (uint32_t)p.n / cs.stride;
+    cs.view_tiles = (uint32_t)p.max_tiles;
+    cs.limit = crowd_limit(cs.per_view, (uint32_t)p.n);
+    sample_blocks = cdiv((uint64_t)cs.views * cs.per_view, kBlock);
+  }
+  hipLaunchKernelGGL(k_depth_range, dim3(gx + cdiv(sample_blocks, gy), gy), dim3(kBlock), 0, s,
+                     p.n, p.ld, p.n_views, proj.depth_bits, proj.tiles_touched, part, vis, icnt,
+                     gx, cs, cams_dev, reinterpret_cast<const uint32_t*>(proj.splat));
   // the depth-bit range and instance count (stats[0..3]); where each
   // chunk's visible pairs go in the depth sort's input (stats[4] = their
   // number), and where each chunk's instances start in emission order,
   // which keeps the views in order (only read once the host has checked
   // that the total fits 32 bits)
-  hipLaunchKernelGGL(k_stage1_close, dim3(4), dim3(kBlock), 0, s, part, vis, icnt, nchunk, stats,
-                     cams_dev, p.n_views, at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv));
-  const DirectPlan d = plan_direct(p, L);
+  hipLaunchKernelGGL(k_stage1_close, dim3(4 + cs.views), dim3(kBlock), 0, s, part, vis, icnt,
+                     nchunk, stats, cams_dev, p.n_views, at<uint32_t>(ws, L.seg_base),
+                     at<int32_t>(ws, L.txv), cs);
   if (d.possible) {
     // the tile counts do not wait for the host
     uint32_t* counts = at<uint32_t>(ws, d.counts);
     uint32_t* rows = at<uint32_t>(ws, d.rows);
-    const uint32_t nseg = (uint32_t)p.n_segments;
     hipLaunchKernelGGL(k_tile_count, dim3(gx, gy), dim3(kChunkThreads), 0, s, p.n, p.ld,
                        p.n_views, proj.tiles_touched, reinterpret_cast<uint32_t*>(proj.splat),
-                       at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), rows);
+                       at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), crowded, rows);
     hipLaunchKernelGGL(k_tile_columns, dim3(cdiv(nseg, 64u)), dim3(1024), 0, s, p.n_views, nseg,
-                       gx, at<uint32_t>(ws, L.seg_base), rows, counts);
+                       gx, at<uint32_t>(ws, L.seg_base), crowded, rows, counts);
     hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nseg,
-                       (uint64_t)p.capacity, stats + 6, stats + kCountsReady,
+                       (uint64_t)p.capacity, crowded, stats + kLongest, stats + kCountsReady,
                        at<uint32_t>(ws, L.total));
   }
   return hipGetLastError();
@@ -1814,8 +1949,8 @@ hipError_t bin_sort_stage2(const BinSortPlan& p, const gs_projected& proj, const
     return hipGetLastError();
   }
   const DirectPlan d = plan_direct(p, L);
-  if (d.possible && stats[6] <= kDirectLongest) {  // filled and sorted already
-    if (stats[6] <= kShortList || p.n_segments <= kWideSortTiles) return hipSuccess;
+  if (d.possible && stats[kLongest] <= kDirectLongest) {  // filled and sorted already
+    if (stats[kLongest] <= kShortList || p.n_segments <= kWideSortTiles) return hipSuccess;
     StageScope scope(kStSegmentSort, s);
     launch_tile_sort(k_tile_sort<256, true>, 256, p, proj, d, L, lists, ws, s);
     return hipGetLastError();

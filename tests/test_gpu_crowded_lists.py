@@ -1,0 +1,90 @@
+"""Jobs whose longest tile list lies on either side of what the direct binning
+sorts, far from it and where the sample that looks for such lists may take
+them for either: the lists are the oracle's whichever route a job takes, also
+when jobs of both kinds follow each other on one context."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_20943_amd import gs, scenes
+from paper_2512_20943_amd.raster import Rasterizer
+from tests.gpu_helpers import lists_to_numpy, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+CAMS = {
+    "one": lambda: scenes.arc_cameras(1, 4.0, 401, 303),
+    "three": lambda: scenes.arc_cameras(3, 4.0, 150, 100),
+    "mixed": lambda: scenes.stack_cams([
+        (c["R"][0], c["t"][0], c["f"][0], tuple(c["wh"][0])) for c in
+        (scenes.arc_cameras(1, 4.0, 64, 48), scenes.arc_cameras(1, 3.5, 401, 303),
+         scenes.arc_cameras(1, 5.0, 97, 65))]),
+}
+
+
+def crowd(n_middle, n_around, mu=-4.5):
+    """n_middle splats on one point, n_around everywhere."""
+    n = n_middle + n_around
+    out = scenes.make_scene(n, n_middle, -1.5, 1.5, mu, 0.4, 0)
+    near = scenes.make_scene(max(n_middle, 1), 3, -0.002, 0.002, -5.0, 0.3, 0)
+    for k in ("mean", "log_scale", "quat", "opacity", "sh"):
+        out[k][..., :n_middle] = near[k][..., :n_middle]
+    return out
+
+
+def check(scene, cams, tileset="spans"):
+    g, gc = gs.Gaussians.from_scene(scene), gs.Cameras(cams)
+    r = Rasterizer(capacity=1 << 21, with_keys=True, tight_rect=tileset != "rect",
+                   tile_spans=tileset == "spans")
+    L_or = oracle.bin_sort(oracle.project(scene, cams, tileset), cams)
+    L_g = lists_to_numpy(r.bin_sort(r.project(g, gc), gc))
+    for k in ("keys", "vals", "ranges"):
+        np.testing.assert_array_equal(L_g[k], L_or[k], err_msg=k)
+    return int(np.diff(L_or["ranges"].astype(np.int64), axis=1).max())
+
+
+# 4,096 entries is the longest list that is sorted directly
+@pytest.mark.parametrize("cams", sorted(CAMS))
+@pytest.mark.parametrize("middle,around", [(5_000, 9_000), (3_000, 60_000), (3_900, 60_000),
+                                           (4_100, 60_000), (6_000, 60_000), (20_000, 5_000)])
+def test_lists_on_both_sides_of_the_limit(middle, around, cams):
+    require_gpu()
+    print(f"crowd {middle} + {around}, {cams}", flush=True)
+    assert check(crowd(middle, around), CAMS[cams]()) >= middle
+
+
+@pytest.mark.parametrize("tileset", ["rect", "spans"])
+def test_crowds_of_splats_over_many_tiles(tileset):
+    """Splats over tens of tiles each, of which the sample counts two."""
+    require_gpu()
+    print(f"crowd of large splats {tileset}", flush=True)
+    longest = check(scenes.make_scene(12_000, 5, -0.3, 0.3, -2.0, 0.3, 0),
+                    scenes.arc_cameras(1, 4.0, 400, 304), tileset)
+    assert longest > 4096
+
+
+def test_crowded_and_ordinary_jobs_in_turn():
+    """Neither kind leaves a word behind that the next call would read."""
+    require_gpu()
+    print("crowded and ordinary jobs in turn", flush=True)
+    jobs = []
+    for scene, c in ((crowd(20_000, 5_000), CAMS["one"]()), (crowd(0, 7_000), CAMS["three"]()),
+                     (crowd(6_000, 30_000), CAMS["mixed"]())):
+        L = oracle.bin_sort(oracle.project(scene, c, "spans"), c)
+        g, gc = gs.Gaussians.from_scene(scene), gs.Cameras(c)
+        proj = gs.Projected.empty(gc.V, g.n, g.ld, "cuda")
+        proj.options = gs.GS_PROJECT_TIGHT_RECT | gs.GS_PROJECT_TILE_SPANS
+        gs.gs_project(gs.default_context(), g, gc, proj)
+        lists = gs.TileLists(L["count"], gc.n_segments(), True)
+        ws = torch.empty(gs.bin_sort_workspace_size(gc.V, g.ld, L["count"], gc.n_segments()),
+                         dtype=torch.uint8, device="cuda")
+        jobs.append((proj, gc, lists, ws, L))
+    for turn in range(30):
+        proj, gc, lists, ws, L = jobs[(turn * turn + turn // 3) % 3]
+        lists.vals.fill_(-3)
+        lists.ranges.fill_(-5)
+        gs.gs_bin_sort(gs.default_context(), proj, gc, lists, ws)
+        got = lists_to_numpy(lists)
+        for k in ("keys", "vals", "ranges"):
+            np.testing.assert_array_equal(got[k], L[k], err_msg=f"turn {turn} {k}")
