@@ -256,6 +256,16 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _scratch(nbytes: int, device, stream):
+    """Scratch for a call's kernels on ``stream`` (None: the current one),
+    allocated there, so that the allocator gives its memory to later work of
+    that stream alone, and takes none that the current stream still uses."""
+    if stream is None:
+        return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
+
+
 class Context:
     """Owns a gs_ctx bound to one device."""
 
@@ -644,8 +654,7 @@ def gs_usage_masks(ctx: Context, usage, n: int, gw: int, gh: int, drops, masks, 
     """masks (len(drops), gh, gw) uint8: mask l is 0 for the drops[l] least
     used of the n Gaussians (equal usage: lower id first) and for padding."""
     levels = len(drops)
-    size = int(ctx.lib.gs_usage_masks_workspace_size(n))
-    ws = torch.empty(max(size, 1), dtype=torch.uint8, device=usage.device)
+    ws = _scratch(int(ctx.lib.gs_usage_masks_workspace_size(n)), usage.device, stream)
     ctx.check(ctx.lib.gs_usage_masks(ctx.handle, _ptr(usage), n, gw, gh,
                                      (c_int32 * levels)(*drops), levels, _ptr(masks), _ptr(ws),
                                      ws.numel(), _stream(stream)))
@@ -656,8 +665,7 @@ def gs_cull_low_opacity(ctx: Context, opacity_logit, n: int, min_opacity: float,
     """Indices of the Gaussians kept by low-opacity culling (written to
     ``kept_index``); returns their number once the indices are complete."""
     if workspace is None:
-        workspace = torch.empty(max(cull_workspace_size(n), 1), dtype=torch.uint8,
-                                device=opacity_logit.device)
+        workspace = _scratch(cull_workspace_size(n), opacity_logit.device, stream)
     out = c_int32(0)
     ctx.check(ctx.lib.gs_cull_low_opacity(ctx.handle, _ptr(opacity_logit), n, float(min_opacity),
                                           _ptr(kept_index), ctypes.byref(out), _ptr(workspace),
