@@ -32,6 +32,7 @@ def test_scratch_is_allocated_on_the_calls_stream(monkeypatch, call, given):
     ctx = types.SimpleNamespace(lib=lib, handle=None, check=lambda st: None)
     monkeypatch.setattr(gs, "load", lambda: lib)
     monkeypatch.setattr(gs, "_stream", lambda s: None)
+    monkeypatch.setattr(gs, "_ptr", lambda t: None)
     monkeypatch.setattr(torch.cuda, "stream", on)
     monkeypatch.setattr(torch, "empty", empty)
     side = object() if given else None
