@@ -1317,11 +1317,30 @@ __global__ __launch_bounds__(64) void k_render_bwd(
 constexpr int kQuadBwdGroup = 4;  // wave_sums9x4 sums four entries
 static_assert(kQuadPad >= kQuadBwdGroup - 1 && kQuadPad >= kQuadGroup - 1, "padding");
 constexpr int kQuadAcc = 9;  // odd stride: the flush reads distinct banks
+// Set in a packed slot when some pixel composited the entry.  An entry that no
+// pixel of the tile did gets a row of zeros, as from one wave per tile.  Its
+// sums are zeros anyhow unless a factor overflows or is not finite, so only a
+// tile where that can happen (`odd`, from the pixels' values on or from the
+// batch on whose records are out of the ordinary) looks at who composites
+// what; every wave of a tile decides the same.
+constexpr int kSlotUsed = 64;
+constexpr int kOddTile = 1 << 30;  // beside a wave's last position
+constexpr float kOddPixel = 1e30f, kOddRecord = 1e7f;  // their product stays finite
+
+__device__ __forceinline__ bool odd_pixel(float T, float g0, float g1, float g2, float S) {
+  return !((fabsf(T) + fabsf(S)) + (fabsf(g0) + fabsf(g1) + fabsf(g2)) < kOddPixel);
+}
+
+__device__ __forceinline__ bool odd_record(float4 q0, float4 q1, float4 q2) {
+  const float r1 = q0.w * __builtin_amdgcn_rcpf(q0.z);
+  return !((fabsf(q0.x) + fabsf(q0.y) + fabsf(r1)) + (fabsf(q1.z) + fabsf(q1.w) + fabsf(q2.x)) <
+           kOddRecord);
+}
 
 struct QuadBwdShared {
   QuadStage st[4];
   float acc[2][4][kQuadSlots * kQuadAcc];
-  int8_t slot[2][4][64];           // an entry's packed slot in a quadrant, or -1
+  int8_t slot[2][4][64];           // an entry's packed slot in a quadrant | kSlotUsed, or -1
   unsigned long long seen[2][4];   // with COUNT, entries a quadrant evaluated
   int wmax[4];
 };
@@ -1389,10 +1408,17 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
   // dL/dcolour . (the colour composited behind the current entry)
   float S = g0 * bg0 + g1 * bg1 + g2 * bg2;
   const int wmax = __builtin_amdgcn_readfirstlane(wave_max(nc));
-  if (lane == 0) sh.wmax[wave] = wmax;
+  const bool odd_wave = __builtin_amdgcn_ballot_w64(odd_pixel(T, g0, g1, g2, S)) != 0;
+  if (lane == 0) sh.wmax[wave] = wmax | (odd_wave ? kOddTile : 0);
   __syncthreads();
-  const int jmax = __builtin_amdgcn_readfirstlane(
-      max(max(sh.wmax[0], sh.wmax[1]), max(sh.wmax[2], sh.wmax[3])));
+  int jm = 0, jo = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    jm = max(jm, sh.wmax[w] & (kOddTile - 1));
+    jo |= sh.wmax[w];
+  }
+  const int jmax = __builtin_amdgcn_readfirstlane(jm);
+  bool odd = (__builtin_amdgcn_readfirstlane(jo) & kOddTile) != 0;
   // where the sums of an entry end up (wave_sums9x4): its value, and the
   // lanes that store one
   const bool u3 = lane & 8, u2 = lane & 4, u1 = lane & 2, u0 = lane & 1;
@@ -1421,6 +1447,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
     const int lo = max(hi - 64, 0);
     const bool have = lo + lane < hi;
     const bool hit = have && lo + lane < wmax && quadrant_hit(q0, q1, q2, ox, oy);
+    odd |= __builtin_amdgcn_ballot_w64(have && odd_record(q0, q1, q2)) != 0;
     const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
     const int count = (int)__popcll(m);
     // packed back to front
@@ -1440,48 +1467,59 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
       if (lane == 0) sh.seen[buf][wave] = m;
     }
     float* acc = sh.acc[buf][wave];
-    for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
-      float au[kQuadBwdGroup], ra[kQuadBwdGroup], gc[kQuadBwdGroup], t[kQuadBwdGroup], dy[kQuadBwdGroup];
-      bool clamped[kQuadBwdGroup];
-      float gr[kQuadBwdGroup][9];
+    unsigned long long used = 0;  // by packed slot, where it is tracked
+    auto walk = [&](auto track) {
+      for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
+        float au[kQuadBwdGroup], ra[kQuadBwdGroup], gc[kQuadBwdGroup], t[kQuadBwdGroup], dy[kQuadBwdGroup];
+        bool clamped[kQuadBwdGroup];
+        float gr[kQuadBwdGroup][9];
 #pragma unroll
-      for (int i = 0; i < kQuadBwdGroup; ++i) {
-        const float4 a = st.a[i0 + i], b = st.b[i0 + i];
-        const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
-        const float dx = (a.x - fx0) - offx;
-        dy[i] = (a.y - fy0) - offy;
-        t[i] = fmaf(a.w, dy[i], dx);
-        const float ea =
-            __builtin_amdgcn_exp2f(fmaf(a.z * t[i], t[i], fmaf(b.x, dy[i] * dy[i], b.y)));
-        const float alpha = fminf(kAlphaMax, ea);
-        const bool use = __float_as_int(c.y) < nc && alpha >= kAlphaMin;
-        clamped[i] = !(ea < kAlphaMax);
-        if constexpr (COUNT) wk_used += (unsigned long long)__popcll(__ballot(use));
-        au[i] = use ? alpha : 0.f;
-        ra[i] = __builtin_amdgcn_rcpf(1.f - au[i]);
-        gc[i] = fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z));
-      }
+        for (int i = 0; i < kQuadBwdGroup; ++i) {
+          const float4 a = st.a[i0 + i], b = st.b[i0 + i];
+          const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
+          const float dx = (a.x - fx0) - offx;
+          dy[i] = (a.y - fy0) - offy;
+          t[i] = fmaf(a.w, dy[i], dx);
+          const float ea =
+              __builtin_amdgcn_exp2f(fmaf(a.z * t[i], t[i], fmaf(b.x, dy[i] * dy[i], b.y)));
+          const float alpha = fminf(kAlphaMax, ea);
+          const bool use = __float_as_int(c.y) < nc && alpha >= kAlphaMin;
+          clamped[i] = !(ea < kAlphaMax);
+          const unsigned long long um = __builtin_amdgcn_ballot_w64(use);
+          if constexpr (track) used |= um != 0 ? 1ull << (i0 + i) : 0ull;
+          if constexpr (COUNT) wk_used += (unsigned long long)__popcll(um);
+          au[i] = use ? alpha : 0.f;
+          ra[i] = __builtin_amdgcn_rcpf(1.f - au[i]);
+          gc[i] = fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z));
+        }
 #pragma unroll
-      for (int i = 0; i < kQuadBwdGroup; ++i) {
-        T = T * ra[i];
-        const float wt = au[i] * T;
-        const float gcb = gc[i] - S;
-        const float gp = clamped[i] ? 0.f : wt * gcb;
-        const float pt = gp * t[i];
-        gr[i][0] = pt;
-        gr[i][1] = gp * dy[i];
-        gr[i][2] = pt * t[i];
-        gr[i][3] = pt * dy[i];
-        gr[i][4] = gr[i][1] * dy[i];
-        gr[i][5] = gp;
-        gr[i][6] = g0 * wt;
-        gr[i][7] = g1 * wt;
-        gr[i][8] = g2 * wt;
-        S = fmaf(au[i], gcb, S);
+        for (int i = 0; i < kQuadBwdGroup; ++i) {
+          T = T * ra[i];
+          const float wt = au[i] * T;
+          const float gcb = gc[i] - S;
+          const float gp = clamped[i] ? 0.f : wt * gcb;
+          const float pt = gp * t[i];
+          gr[i][0] = pt;
+          gr[i][1] = gp * dy[i];
+          gr[i][2] = pt * t[i];
+          gr[i][3] = pt * dy[i];
+          gr[i][4] = gr[i][1] * dy[i];
+          gr[i][5] = gp;
+          gr[i][6] = g0 * wt;
+          gr[i][7] = g1 * wt;
+          gr[i][8] = g2 * wt;
+          S = fmaf(au[i], gcb, S);
+        }
+        // the padding's sums go to slots that no entry has
+        const float rs = wave_sums9x4(gr, u1, u0);
+        if (acc_writer) acc[i0 * kQuadAcc + acc_lane] = rs;
       }
-      // the padding's sums go to slots that no entry has
-      const float rs = wave_sums9x4(gr, u1, u0);
-      if (acc_writer) acc[i0 * kQuadAcc + acc_lane] = rs;
+    };
+    if (odd) {
+      walk(std::true_type{});
+      if (hit && ((used >> slot) & 1)) sh.slot[buf][wave][lane] = (int8_t)(slot | kSlotUsed);
+    } else {
+      walk(std::false_type{});
     }
     __syncthreads();
     if constexpr (COUNT) {
@@ -1493,11 +1531,17 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
     }
     if (wave == turn && have) {
       float mom[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      bool add = true;
+      if (odd) {
+        int any = 0;
+        for (int w = 0; w < 4; ++w) any |= max((int)sh.slot[buf][w][lane], 0);
+        add = (any & kSlotUsed) != 0;
+      }
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const int at = sh.slot[buf][w][lane];
-        if (at >= 0) {
-          const float* a = sh.acc[buf][w] + at * kQuadAcc;
+        if (at >= 0 && add) {
+          const float* a = sh.acc[buf][w] + (at & (kSlotUsed - 1)) * kQuadAcc;
 #pragma unroll
           for (int cc = 0; cc < 9; ++cc) mom[cc] += a[cc];
         }
@@ -1534,7 +1578,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
 struct OctBwdShared {
   QuadStage st[8];
   float acc[2][8][kQuadSlots * kQuadAcc];
-  int8_t slot[2][8][64];           // an entry's packed slot in a half, or -1
+  int8_t slot[2][8][64];           // an entry's packed slot in a half | kSlotUsed, or -1
   unsigned long long seen[2][8];   // with COUNT, entries a half evaluated
   int wmax[8];
 };
@@ -1576,12 +1620,17 @@ __global__ __launch_bounds__(512) void k_render_bwd_octs(
   // dL/dcolour . (the colour composited behind the current entry)
   float S = g0 * bg0 + g1 * bg1 + g2 * bg2;
   const int wmax = __builtin_amdgcn_readfirstlane(wave_max(nc));
-  if (lane == 0) sh.wmax[wave] = wmax;
+  const bool odd_wave = __builtin_amdgcn_ballot_w64(odd_pixel(T, g0, g1, g2, S)) != 0;
+  if (lane == 0) sh.wmax[wave] = wmax | (odd_wave ? kOddTile : 0);
   __syncthreads();
-  int jm = 0;
+  int jm = 0, jo = 0;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) jm = max(jm, sh.wmax[w]);
+  for (int w = 0; w < 8; ++w) {
+    jm = max(jm, sh.wmax[w] & (kOddTile - 1));
+    jo |= sh.wmax[w];
+  }
   const int jmax = __builtin_amdgcn_readfirstlane(jm);
+  bool odd = (__builtin_amdgcn_readfirstlane(jo) & kOddTile) != 0;
   // where the sums of an entry end up (wave_sums9x4): its value, and the
   // lanes that store one
   const bool u3 = lane & 8, u2 = lane & 4, u1 = lane & 2, u0 = lane & 1;
@@ -1610,6 +1659,7 @@ __global__ __launch_bounds__(512) void k_render_bwd_octs(
     const int lo = max(hi - 64, 0);
     const bool have = lo + lane < hi;
     const bool hit = have && lo + lane < wmax && quadrant_hit<4>(q0, q1, q2, ox, oy);
+    odd |= __builtin_amdgcn_ballot_w64(have && odd_record(q0, q1, q2)) != 0;
     const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
     const int count = (int)__popcll(m);
     // packed back to front
@@ -1628,53 +1678,67 @@ __global__ __launch_bounds__(512) void k_render_bwd_octs(
       if (lane == 0) sh.seen[buf][wave] = m;
     }
     float* acc = sh.acc[buf][wave];
-    for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
-      float gr[2][9];
+    unsigned long long used = 0;  // by packed slot, where it is tracked
+    auto walk = [&](auto track) {
+      for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
+        float gr[2][9];
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int at = i0 + 2 * p + (int)upper;
-        const float4 a = st.a[at], b = st.b[at];
-        const float2 c = *reinterpret_cast<const float2*>(&st.c[at]);
-        const float dx = (a.x - fx0) - offx, dy = (a.y - fy0) - offy;
-        const float t = fmaf(a.w, dy, dx);
-        const float ea = __builtin_amdgcn_exp2f(fmaf(a.z * t, t, fmaf(b.x, dy * dy, b.y)));
-        const float alpha = fminf(kAlphaMax, ea);
-        const bool use = __float_as_int(c.y) < nc && alpha >= kAlphaMin;
-        if constexpr (COUNT) wk_used += (unsigned long long)__popcll(__ballot(use));
-        const float au = use ? alpha : 0.f;
-        float au0, au1, ra0, ra1, gc0, gc1;
-        both_halves(au, au0, au1);
-        both_halves(__builtin_amdgcn_rcpf(1.f - au), ra0, ra1);
-        both_halves(fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z)), gc0, gc1);
-        // the pair in order, on every lane; each half keeps its own entry's
-        const float T0 = T * ra0;
-        T = T0 * ra1;
-        const float d0 = gc0 - S;
-        S = fmaf(au0, d0, S);
-        const float d1 = gc1 - S;
-        S = fmaf(au1, d1, S);
-        const float wt = au * (upper ? T : T0);
-        const float gcb = upper ? d1 : d0;
-        const float gp = ea < kAlphaMax ? wt * gcb : 0.f;
-        const float pt = gp * t;
-        gr[p][0] = pt;
-        gr[p][1] = gp * dy;
-        gr[p][2] = pt * t;
-        gr[p][3] = pt * dy;
-        gr[p][4] = gr[p][1] * dy;
-        gr[p][5] = gp;
-        gr[p][6] = g0 * wt;
-        gr[p][7] = g1 * wt;
-        gr[p][8] = g2 * wt;
+        for (int p = 0; p < 2; ++p) {
+          const int at = i0 + 2 * p + (int)upper;
+          const float4 a = st.a[at], b = st.b[at];
+          const float2 c = *reinterpret_cast<const float2*>(&st.c[at]);
+          const float dx = (a.x - fx0) - offx, dy = (a.y - fy0) - offy;
+          const float t = fmaf(a.w, dy, dx);
+          const float ea = __builtin_amdgcn_exp2f(fmaf(a.z * t, t, fmaf(b.x, dy * dy, b.y)));
+          const float alpha = fminf(kAlphaMax, ea);
+          const bool use = __float_as_int(c.y) < nc && alpha >= kAlphaMin;
+          const unsigned long long um = __builtin_amdgcn_ballot_w64(use);
+          if constexpr (track) {
+            used |= (uint32_t)um != 0 ? 1ull << (i0 + 2 * p) : 0ull;
+            used |= (uint32_t)(um >> 32) != 0 ? 2ull << (i0 + 2 * p) : 0ull;
+          }
+          if constexpr (COUNT) wk_used += (unsigned long long)__popcll(um);
+          const float au = use ? alpha : 0.f;
+          float au0, au1, ra0, ra1, gc0, gc1;
+          both_halves(au, au0, au1);
+          both_halves(__builtin_amdgcn_rcpf(1.f - au), ra0, ra1);
+          both_halves(fmaf(g2, c.x, fmaf(g1, b.w, g0 * b.z)), gc0, gc1);
+          // the pair in order, on every lane; each half keeps its own entry's
+          const float T0 = T * ra0;
+          T = T0 * ra1;
+          const float d0 = gc0 - S;
+          S = fmaf(au0, d0, S);
+          const float d1 = gc1 - S;
+          S = fmaf(au1, d1, S);
+          const float wt = au * (upper ? T : T0);
+          const float gcb = upper ? d1 : d0;
+          const float gp = ea < kAlphaMax ? wt * gcb : 0.f;
+          const float pt = gp * t;
+          gr[p][0] = pt;
+          gr[p][1] = gp * dy;
+          gr[p][2] = pt * t;
+          gr[p][3] = pt * dy;
+          gr[p][4] = gr[p][1] * dy;
+          gr[p][5] = gp;
+          gr[p][6] = g0 * wt;
+          gr[p][7] = g1 * wt;
+          gr[p][8] = g2 * wt;
+        }
+        // rows 0 and 1 of the wave hold the first entries' pixels, rows 2 and 3
+        // the second ones'
+        float y9[9];
+#pragma unroll
+        for (int cc = 0; cc < 9; ++cc) y9[cc] = pair_rows(gr[0][cc], gr[1][cc]);
+        // the padding's sums go to slots that no entry has
+        const float rs = row_sums9(y9, u1, u0);
+        if (acc_writer) acc[i0 * kQuadAcc + acc_lane] = rs;
       }
-      // rows 0 and 1 of the wave hold the first entries' pixels, rows 2 and 3
-      // the second ones'
-      float y9[9];
-#pragma unroll
-      for (int cc = 0; cc < 9; ++cc) y9[cc] = pair_rows(gr[0][cc], gr[1][cc]);
-      // the padding's sums go to slots that no entry has
-      const float rs = row_sums9(y9, u1, u0);
-      if (acc_writer) acc[i0 * kQuadAcc + acc_lane] = rs;
+    };
+    if (odd) {
+      walk(std::true_type{});
+      if (hit && ((used >> slot) & 1)) sh.slot[buf][wave][lane] = (int8_t)(slot | kSlotUsed);
+    } else {
+      walk(std::false_type{});
     }
     __syncthreads();
     if constexpr (COUNT) {
@@ -1692,11 +1756,17 @@ __global__ __launch_bounds__(512) void k_render_bwd_octs(
     }
     if (wave == turn && have) {
       float mom[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      bool add = true;
+      if (odd) {
+        int any = 0;
+        for (int w = 0; w < 8; ++w) any |= max((int)sh.slot[buf][w][lane], 0);
+        add = (any & kSlotUsed) != 0;
+      }
 #pragma unroll
       for (int w = 0; w < 8; ++w) {
         const int at = sh.slot[buf][w][lane];
-        if (at >= 0) {
-          const float* a = sh.acc[buf][w] + at * kQuadAcc;
+        if (at >= 0 && add) {
+          const float* a = sh.acc[buf][w] + (at & (kSlotUsed - 1)) * kQuadAcc;
 #pragma unroll
           for (int cc = 0; cc < 9; ++cc) mom[cc] += a[cc];
         }
