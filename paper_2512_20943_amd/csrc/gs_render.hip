@@ -774,7 +774,9 @@ __device__ __forceinline__ void both_halves(float x, float& lower, float& upper)
   upper = __uint_as_float(p[1]);
 }
 
-template <bool CLAMP>
+// BRANCH: skip entries that no pixel uses, for batches with a colour that is
+// not finite: 0 times it would reach pixels that have stopped before it.
+template <bool CLAMP, bool BRANCH>
 __device__ __forceinline__ void oct_walk(const QuadStage& st, int count, float fx0, float fy0,
                                          float offx, float offy, QuadPixel& px) {
   const int half = (threadIdx.x & 63) >> 5;
@@ -794,6 +796,7 @@ __device__ __forceinline__ void oct_walk(const QuadStage& st, int count, float f
     for (int i = 0; i < 4; ++i) {
       const unsigned long long use =
           px.live & __builtin_amdgcn_ballot_w64(alpha[i] >= kAlphaMin);
+      if (BRANCH && use == 0) continue;
       const float2 rg = *reinterpret_cast<const float2*>(&st.b[i0 + i].z);
       const float2 c = *reinterpret_cast<const float2*>(&st.c[i0 + i]);
       const float Tn = px.T * (1.f - alpha[i]);
@@ -848,17 +851,22 @@ __global__ __launch_bounds__(512) void k_render_fwd_octs(
   QuadStage& st = sh[wave];
   for (uint32_t b0 = rg.x; b0 < rg.y && px.live != 0; b0 += 64, e += 64) {
     const bool hit = e < rg.y && quadrant_hit<4>(q0, q1, q2, ox, oy);
+    const bool odd = !(q1.z + q1.w + q2.x < __builtin_inff());
+    const unsigned long long special =
+        __builtin_amdgcn_ballot_w64(hit && (odd || !(q1.y < 0.98f)));
+    const bool branch = (special & __builtin_amdgcn_ballot_w64(odd)) != 0;
     const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
     const int count = (int)__popcll(m);
     quad_stage(st, q0, q1, q2, hit, lanes_below(m), count, (int)(e - rg.x) + 1);
-    const bool clamp = __builtin_amdgcn_ballot_w64(hit && !(q1.y < 0.98f)) != 0;
     if (e + 64 < rg.y) load(gn);
     gn = e + 128 < rg.y ? vals[e + 128] : 0u;
     wave_lds_fence();
-    if (clamp)
-      oct_walk<true>(st, count, fx0, fy0, offx, offy, px);
+    if (special == 0)
+      oct_walk<false, false>(st, count, fx0, fy0, offx, offy, px);
+    else if (!branch)
+      oct_walk<true, false>(st, count, fx0, fy0, offx, offy, px);
     else
-      oct_walk<false>(st, count, fx0, fy0, offx, offy, px);
+      oct_walk<true, true>(st, count, fx0, fy0, offx, offy, px);
     wave_lds_fence();
   }
   float4 dabs = make_float4(0.f, 0.f, 0.f, 0.f);
