@@ -6,10 +6,10 @@
 // chunk of Gaussians land on one XCD (workgroups are dealt to the 8 XCDs
 // round-robin by index), so the SoA parameters (56 B at SH degree 0, 236 B
 // at degree 3) come from HBM once and from that XCD's L2 for the other
-// groups, while the view groups multiply the waves in flight.  The quantities that
-// decide integers downstream -- depth key, radius, tile rectangle -- are
-// evaluated in FP64 with contraction off and a fixed operation order, so
-// that tile lists are reproducible exactly.  Colour is FP32.
+// groups, while the view groups multiply the waves in flight.  The quantities
+// that decide integers downstream -- depth key, radius, tile rectangle -- are
+// evaluated in FP64 with contraction off and a fixed operation order, so that
+// tile lists are reproducible exactly.  Colour is FP32.
 //
 // The kernel is bound by the issue of its FP64 instructions, so quotients by
 // one denominator share its reciprocal, a view's constants are formed once
@@ -98,9 +98,12 @@ __device__ __forceinline__ double clampd(double x, double lo, double hi) {
 
 // Quotients by one denominator: the IEEE division sequence (reciprocal, two
 // Newton steps, quotient, remainder, correction) with the steps that depend on
-// the denominator alone done once.  Correctly rounded, the bits of a / b,
-// while neither side is near the ends of the exponent range (the full division
-// scales its operands there): callers check that and divide otherwise.
+// the denominator alone done once.  Correctly rounded, the bits of a / b, for
+// normal operands away from the ends of the exponent range (the full division
+// scales them there).  Callers check the upper end and divide otherwise.  At
+// the lower one a numerator below 2^-900 or so may come out an ulp off, and
+// -0 as +0: what they are added to (a coordinate's centre, the entries of a
+// covariance that is dilated by 0.3) leaves no trace of either in a record.
 constexpr double kQuotMax = 1e150;
 
 __device__ __forceinline__ double quot_recip(double b) {
@@ -226,15 +229,15 @@ __global__ __launch_bounds__(256) void k_project(
       double Vm[9];
       {
         double T1[9];
-  #pragma unroll
+#pragma unroll
         for (int r = 0; r < 3; ++r)
-  #pragma unroll
+#pragma unroll
           for (int c = 0; c < 3; ++c)
             T1[3 * r + c] = (R[3 * r + 0] * S[0 * 3 + c] + R[3 * r + 1] * S[1 * 3 + c]) +
                             R[3 * r + 2] * S[2 * 3 + c];
-  #pragma unroll
+#pragma unroll
         for (int r = 0; r < 3; ++r)
-  #pragma unroll
+#pragma unroll
           for (int c = 0; c < 3; ++c)
             Vm[3 * r + c] = (T1[3 * r + 0] * R[3 * c + 0] + T1[3 * r + 1] * R[3 * c + 1]) +
                             T1[3 * r + 2] * R[3 * c + 2];
@@ -514,7 +517,8 @@ __global__ __launch_bounds__(256) void k_project_bwd(
   // flags a view earlier still): with two waves per SIMD the loop otherwise
   // waits for two dependent loads per view.  300 k Gaussians in 20 views 195
   // -> 169 us, 2 M in 8 views 484 -> 384 (214 at the copy rate for its 1.0
-  // GB), 300 k in one view 32.5 -> 32.9.
+  // GB), 300 k in one view 32.5 -> 32.9.  Counted traffic at 20 views
+  // grew with it, 668 -> 760 MB.
   struct {
     float4 ga, gb, gc;
     float A, B, C;
