@@ -260,6 +260,11 @@ const char* gs_stage_name(int stage);
  *   2 fwd slot evaluations, 3 fwd pairs with T > 0 and alpha >= 1/255,
  *   4 bwd entries staged, 5 bwd entries visited, 6 bwd slot evaluations,
  *   7 bwd pairs inside the pixel's list prefix with alpha >= 1/255.
+ * The backward counts in the kernel that the launch would run; where that
+ * evaluates half quadrants (up to 640 tiles), 6 counts the quadrants.  The
+ * forward counts in the kernel of one wave per tile at every size: up to
+ * 36,000 tiles, where others run, its counters are the path's work and not
+ * the running kernel's, and do not go with its times.
  * The counting kernels are slower (one 64-bit atomic per counter per tile)
  * and are meant for runs outside any timed region.  NULL switches counting
  * off.  Other calls ignore the setting. */
