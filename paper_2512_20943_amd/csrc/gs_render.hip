@@ -5,12 +5,11 @@
 // ones: four waves per tile, one per 8x8 quadrant; the smallest: eight, two
 // per quadrant (see the kernels of those names).  With one wave per tile, lane
 // l owns pixel (l & 7, l >> 3) of each of the tile's four 8x8 quadrants
-// ("slots"), so a
-// slot is a compact 64-pixel block.  The tile's instance list is walked in
-// batches staged in LDS (the forward one record per lane, the backward one
-// per two lanes).  While staging a record, its lane also tests the
-// Gaussian's alpha >= 1/255 ellipse against each quadrant's pixel box (exact
-// box minimum of the quadratic form, with a conservative margin); the
+// ("slots"), so a slot is a compact 64-pixel block.  The tile's instance list
+// is walked in batches staged in LDS (the forward one record per lane, the
+// backward one per two lanes).  While staging a record, its lane also tests
+// the Gaussian's alpha >= 1/255 ellipse against each quadrant's pixel box
+// (exact box minimum of the quadratic form, with a conservative margin); the
 // results are kept as one wave ballot per quadrant, and the wave walks the
 // set bits, skipping, uniformly, every slot whose quadrant the ellipse
 // misses, which is exact because every such pair would be skipped per pixel
@@ -27,9 +26,9 @@
 // one row sum per lane (22 instructions, one LDS store), adds the four row
 // sums when the batch is flushed, and writes one 9-float gradient row per
 // (tile, Gaussian) at the instance's index in the binning's emission order.
-// A second kernel sums
-// each (view, Gaussian)'s rows, which that order keeps contiguous: no
-// floating-point atomics, and the result does not depend on scheduling.
+// A second kernel sums each (view, Gaussian)'s rows, which that order keeps
+// contiguous: no floating-point atomics, and the result does not depend on
+// scheduling.
 #include <algorithm>
 
 #include "gs_internal.h"
@@ -882,7 +881,8 @@ __global__ __launch_bounds__(512) void k_render_fwd_octs(
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
         d[ch] = o[ch] - target[3 * pix * v + ch * pix + p];
-        grad[3 * pix * v + ch * pix + p] = d[ch] > 0.f ? inv_count : (d[ch] < 0.f ? -inv_count : 0.f);
+        grad[3 * pix * v + ch * pix + p] =
+            d[ch] > 0.f ? inv_count : (d[ch] < 0.f ? -inv_count : 0.f);
       }
       dabs = make_float4(fabsf(d[0]), fabsf(d[1]), fabsf(d[2]), 0.f);
     }
@@ -1318,10 +1318,11 @@ __global__ __launch_bounds__(64) void k_render_bwd(
 // waves, one per quadrant, which walk the same batches of 64 entries back to
 // front, each over the packed entries its own quadrant needs, four at a time
 // (their alphas, reciprocals and colour products are independent; the
-// transmittance and the colour behind are serial).  A wave sums the four entries' nine values over its 64 pixels
-// together and stores them; after the batch's one barrier the wave whose
-// turn it is adds the quadrants' sums and writes the rows, while the others
-// go on with the next batch into the other buffer.
+// transmittance and the colour behind are serial).  A wave sums the four
+// entries' nine values over its 64 pixels together and stores them; after the
+// batch's one barrier the wave whose turn it is adds the quadrants' sums and
+// writes the rows, while the others go on with the next batch into the other
+// buffer.
 constexpr int kQuadBwdGroup = 4;  // wave_sums9x4 sums four entries
 static_assert(kQuadPad >= kQuadBwdGroup - 1 && kQuadPad >= kQuadGroup - 1, "padding");
 constexpr int kQuadAcc = 9;  // odd stride: the flush reads distinct banks
@@ -1478,7 +1479,8 @@ __global__ __launch_bounds__(256) void k_render_bwd_quads(
     unsigned long long used = 0;  // by packed slot, where it is tracked
     auto walk = [&](auto track) {
       for (int i0 = 0; i0 < count; i0 += kQuadBwdGroup) {
-        float au[kQuadBwdGroup], ra[kQuadBwdGroup], gc[kQuadBwdGroup], t[kQuadBwdGroup], dy[kQuadBwdGroup];
+        float au[kQuadBwdGroup], ra[kQuadBwdGroup], gc[kQuadBwdGroup];
+        float t[kQuadBwdGroup], dy[kQuadBwdGroup];
         bool clamped[kQuadBwdGroup];
         float gr[kQuadBwdGroup][9];
 #pragma unroll
@@ -2050,9 +2052,8 @@ void launch_render_fwd_l1(const gs_projected& proj, const gs_tile_lists& lists, 
 }
 
 size_t render_batched_workspace_bytes(int V) {
-  return 256 + 256 * ((((size_t)V + 1) * 4 + 255) / 256) +
-         256 * ((((size_t)V + 1) * 8 + 255) / 256) +
-         256 * (((size_t)V * 8 + 255) / 256);
+  return 256 * ((((size_t)V + 1) * 4 + 255) / 256) +
+         256 * ((((size_t)V + 1) * 8 + 255) / 256) + 256 * (((size_t)V * 8 + 255) / 256);
 }
 
 void launch_render_batched(const gs_projected& proj, const gs_tile_lists& lists,

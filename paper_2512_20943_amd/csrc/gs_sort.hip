@@ -822,8 +822,10 @@ __global__ __launch_bounds__(kBlock) void k_stage1_close(
 // its own search: one 1280x720 view 75 -> 19 us, twelve views 221 -> 106, 2 M
 // Gaussians in 8 views 322 -> 181; the 20-view frame (32 M instances), whose
 // views hold no large splats, 185 -> 178: what is left there is the random
-// 64-B record each entry reads and writes.  With pack >= 0 each instance is one word, tile <<
-// pack | id, in seg_out (id_out unused).
+// 64-B record each entry reads and writes.  It pays with traffic, there 789 ->
+// 898 MB counted and 61 k -> 245 k waves, three of four workgroups finding
+// nothing to share.  With pack >= 0 each instance is one word, tile << pack |
+// id, in seg_out (id_out unused).
 constexpr uint32_t kEmitShare = 8192;  // instances from which a range is shared
 
 template <typename K>
@@ -1531,7 +1533,7 @@ inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b
 
 struct Layout {
   size_t dk0, dk1, dv0, dv1, cnt, chunks, segk0, segk1, segv_alt, pcount, dtotal,
-      pfirst, pdesc, dparts, vparts, iparts, seg_base, txv, total, stats, bytes;
+      pfirst, pdesc, dparts, vparts, iparts, seg_base, txv, total, bytes;
 };
 
 // Bound on the partitions of n keys cut per view (at most one partial
@@ -1568,9 +1570,6 @@ Layout make_layout(int V, int ld, int64_t cap, int64_t nseg) {
   L.seg_base = take(((size_t)V + 1) * 4);
   L.txv = take((size_t)V * 4);
   L.total = take(16);
-  // {min bits, max bits, instances lo, hi, visible pairs, instances (low
-  // word, scanned)}
-  L.stats = take(32);
   const size_t nchunk = (size_t)V * cdiv((uint64_t)ld, kCountChunk);
   L.dparts = take(nchunk * 16);
   L.vparts = take((nchunk + 1) * 4);
