@@ -66,7 +66,15 @@ __global__ __launch_bounds__(kResidualThreads) void k_residual(
       a[c] = load_pack<N>(D + first + c * plane);
       b[c] = load_pack<N>(P + first + c * plane);
     }
-    const Pack<N, uint8_t> m = load_pack<N>(mask + t);
+    // the mask counts at texels i < n only, and may end there
+    Pack<N, uint8_t> m{};
+    if (t + N <= (size_t)n) {
+      m = load_pack<N>(mask + t);
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (t + k < (size_t)n) m.x[k] = mask[t + k];
+    }
 #pragma unroll
     for (int c = 0; c < kOwn; ++c) {
       Pack<N, float> v;
