@@ -153,13 +153,22 @@ struct Renderer {
     return (size_t)(reinterpret_cast<char*>(p) - static_cast<char*>(base)) + bytes <= size;
   }
 
+  // As render_batch; after a failure nothing of the batch is in flight any
+  // more: kernels that were launched write to the caller's images and read
+  // the uploads that the next batch replaces.
+  gs_status render(const gs_request* reqs, const int* idx, int B, float* const* out) {
+    const gs_status st = render_batch(reqs, idx, B, out);
+    if (st != GS_OK) (void)hipStreamSynchronize(stream);
+    return st;
+  }
+
   // Render requests reqs[idx[0..B)]; out (nullable) holds one device
   // pointer per request index for its (3, H, W) image.  Images are rendered
   // in place (twelve requests of 640x480 to 1920x1080: 1,593 us, 1,697 with
   // copies from a buffer of the renderer's own).  Only a pointer that a
   // kernel may not write, or one whose image overlaps another of the batch,
   // still gets a copy, in the batch's order.
-  gs_status render(const gs_request* reqs, const int* idx, int B, float* const* out) {
+  gs_status render_batch(const gs_request* reqs, const int* idx, int B, float* const* out) {
     const int ld = seq->anchor.ld;
     const int n = seq->anchor.n;
     // requests grouped by frame (stable)
@@ -284,7 +293,8 @@ struct Renderer {
                                 hipMemcpyDeviceToDevice, stream),
                  "image copy");
     GS_SRV_HIP(hipStreamSynchronize(stream), "stream synchronise");
-    inst_per_tile = 0.8 * inst_per_tile + 0.2 * (double)lists.count / (double)std::max<size_t>(tiles_total, 1);
+    inst_per_tile = 0.8 * inst_per_tile +
+                    0.2 * (double)lists.count / (double)std::max<size_t>(tiles_total, 1);
     return GS_OK;
   }
 #undef GS_SRV_TRY
