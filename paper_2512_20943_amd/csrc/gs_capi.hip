@@ -458,7 +458,7 @@ gs_status gs_bin_sort(gs_ctx* c, const gs_projected* proj, const gs_camera* ch,
     e = gs::bin_sort_ahead(plan, *proj, *lists, ws, &ahead, s);
     if (e != hipSuccess) return hip_fail(c, e, "bin_sort (fill)");
     auto told = [&](int k) { return __atomic_load_n(stats + k, __ATOMIC_ACQUIRE) != 0; };
-    auto by_radix = [&] { return !ahead || told(gs::kCrowded); };
+    auto by_radix = [&] { return !ahead || told(gs::kLeaveDirect); };
     e = wait_words(
         [&] {
           constexpr int k = gs::kTotalsReady;

@@ -107,11 +107,11 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
 // Words of the pinned stats by which the device tells the host what it has
 // written there: kCountsReady, by the direct route's scan, all of them;
 // kTotalsReady + 0, 1 and 2, by the end of stage 1, stats[0..3], [4] and [5];
-// kCrowded, by the end of stage 1 too, that a list is taken to be too long for
-// the direct route, whose kernels then do nothing and tell nothing.  A call
-// returns only when nothing of it will write to a word any more.
+// kLeaveDirect, by the end of stage 1 too, that the job is not for the direct
+// route, whose kernels then do nothing and tell nothing.  A call returns only
+// when nothing of it will write to a word any more.
 constexpr int kStatWords = 16;
-constexpr int kLongest = 6, kCountsReady = 7, kTotalsReady = 8, kCrowded = 11;
+constexpr int kLongest = 6, kCountsReady = 7, kTotalsReady = 8, kLeaveDirect = 11;
 __device__ __forceinline__ void tell_host(uint32_t* word) {
   __threadfence_system();
   __hip_atomic_store(word, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

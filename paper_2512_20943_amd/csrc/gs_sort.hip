@@ -487,15 +487,18 @@ constexpr uint32_t kDirectLongest = 4096;  // keys a sorting workgroup holds
 // the direct route's launches, which do nothing).  Jobs that stay pay 2-3 us.
 // One pair in 64 because a list of 4,097 then has 64 +- 8 pairs in the sample;
 // counters of all XCDs in memory in place of one workgroup's took 25-100 us.
+// Lists of wide splats need no sample: they are as long as the job is large
+// (kDirectCost).
 constexpr uint32_t kSampleEvery = 64;     // of all views together one pair in as many,
 constexpr uint32_t kSampleLeast = 2048, kSampleMost = 16384;  // within these
-constexpr uint32_t kSampleWeight = 7;     // most tiles that one of a pair's two stands for
+constexpr uint32_t kSampleMostTiles = 4;  // of a pair; wider ones spread over many lists
 static_assert(kChunkTiles <= 1 << 13, "13 bits per tile of a sampled pair");
 
 struct CrowdSample {
   uint32_t* tiles;    // per sampled pair: two tiles of 13 bits, their number (2 bits), weight
-  uint32_t* crowded;  // device flag
-  uint32_t views, per_view;
+  uint32_t* leave;    // device flag: the job is left to the radix sorts
+  bool direct;        // the job takes the direct route unless it is left
+  uint32_t views, per_view;  // of the sample; none: no list can be too long
   uint32_t stride;      // Gaussians per sampled one
   uint32_t view_tiles;  // most tiles of a view
   uint32_t limit;       // weighted pairs of one tile from which on it is crowded
@@ -516,11 +519,11 @@ __device__ __forceinline__ void crowd_sample(const CrowdSample& cs, uint32_t k, 
   const uint4 en = emit_entry(splat_words + at * (4 * kSplatF4) + 12, i, tx);
   const uint32_t nt = (uint32_t)max(tiles[at], 0);
   uint32_t out = 0;
-  if (nt > 0) {
+  if (nt > 0 && nt <= kSampleMostTiles) {
     const uint32_t l0 = __umulhi(h * 747796405u, nt), l = l0 + nt / 2;
     out = entry_tile(en, tx, l0) & (kChunkTiles - 1);
     out |= (entry_tile(en, tx, l < nt ? l : l - nt) & (kChunkTiles - 1)) << 13;
-    out |= min(nt, 2u) << 26 | min(max(nt / 2, 1u), kSampleWeight) << 28;
+    out |= min(nt, 2u) << 26 | max(nt / 2, 1u) << 28;
   }
   cs.tiles[k] = out;
 }
@@ -528,8 +531,10 @@ __device__ __forceinline__ void crowd_sample(const CrowdSample& cs, uint32_t k, 
 // One workgroup adds up view v's sample.  The one thread that raises the flag
 // tells the host, so nothing else of the call writes that word.
 __device__ __forceinline__ void crowd_count(const CrowdSample& cs, uint32_t v,
-                                            uint32_t* __restrict__ crowded_host) {
-  __shared__ uint32_t s_count[kChunkTiles];
+                                            uint32_t* __restrict__ leave_host) {
+  __shared__ uint4 s_four[kChunkTiles / 4];
+  uint32_t* s_count = reinterpret_cast<uint32_t*>(s_four);
+  const uint32_t fours = (cs.view_tiles + 3) / 4;
   const uint32_t* mine = cs.tiles + (size_t)v * cs.per_view;
   constexpr uint32_t kAhead = 24;
   uint32_t x[kAhead];
@@ -539,7 +544,7 @@ __device__ __forceinline__ void crowd_count(const CrowdSample& cs, uint32_t v,
       x[u] = j0 + u * kBlock < cs.per_view ? mine[j0 + u * kBlock] : 0;
   };
   load(threadIdx.x);
-  for (uint32_t t = threadIdx.x; t < cs.view_tiles; t += kBlock) s_count[t] = 0u;
+  for (uint32_t t = threadIdx.x; t < fours; t += kBlock) s_four[t] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   for (uint32_t j0 = threadIdx.x; j0 < cs.per_view;) {
 #pragma unroll
@@ -553,9 +558,12 @@ __device__ __forceinline__ void crowd_count(const CrowdSample& cs, uint32_t v,
   }
   __syncthreads();
   uint32_t most = 0;
-  for (uint32_t t = threadIdx.x; t < cs.view_tiles; t += kBlock) most = max(most, s_count[t]);
-  if (__syncthreads_or(most >= cs.limit) && threadIdx.x == 0 && atomicExch(cs.crowded, 1u) == 0)
-    tell_host(crowded_host);
+  for (uint32_t t = threadIdx.x; t < fours; t += kBlock) {
+    const uint4 q = s_four[t];
+    most = max(max(most, max(q.x, q.y)), max(q.z, q.w));
+  }
+  if (__syncthreads_or(most >= cs.limit) && threadIdx.x == 0 && atomicExch(cs.leave, 1u) == 0)
+    tell_host(leave_host);
 }
 
 // Per chunk of kCountChunk Gaussians of one view (grid x; views on grid y,
@@ -581,7 +589,7 @@ __global__ __launch_bounds__(kBlock) void k_depth_range(int n, int ld, int V,
     crowd_sample(cs, b * kBlock + threadIdx.x, ld, cams, tiles, splat_words);
     return;
   }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *cs.crowded = 0u;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *cs.leave = 0u;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool vec = rows_aligned(ld, tiles, depth_bits);
   for (int v = blockIdx.y; v < V; v += gridDim.y) {
@@ -627,33 +635,49 @@ __global__ __launch_bounds__(kBlock) void k_depth_range(int n, int ld, int V,
   }
 }
 
+// The direct route's time beyond what both routes take grows with the
+// instances of its largest chunk, which one workgroup counts and fills (0.92
+// ns each), and with all of them (10.5 ns per thousand more than the radix
+// sorts).  A job is left where their sum, in the first's units, passes this:
+// gs_bin_sort in us, direct / radix, of splats over tens to hundreds of tiles:
+// 8 k Gaussians, 90 k instances in the largest chunk, 0.35 M in all 129 / 149;
+// 188 k, 0.73 M 226 / 146; 2 k, 6.7 M, 6.7 M 6,340 / 300; 60 k, 80 k, 2.2 M
+// 142 / 168; 93 k, 2.6 M 183 / 174; 200 k, 39 k, 3.6 M 149 / 176; 80 k, 7.5 M
+// 270 / 218; 15.5 k, 4.4 M 185 / 218; 33 k, 9.4 M 326 / 267.
+constexpr uint64_t kDirectCost = 105000, kDirectShare = 125;
+
 // stats = {min bits, max bits, count lo, count hi} over the per-block
 // partials of k_depth_range, by one block (device-wide atomics on three
-// addresses from every block serialise at the memory side).
-__device__ __forceinline__ void stats_reduce(const uint4* __restrict__ part, int nb,
-                                             uint32_t* __restrict__ stats) {
-  __shared__ uint32_t s_min[4], s_max[4];
+// addresses from every block serialise at the memory side).  Thread 0 gets
+// the job's cost on the direct route.
+__device__ __forceinline__ uint32_t stats_reduce(const uint4* __restrict__ part, int nb,
+                                                 uint32_t* __restrict__ stats) {
+  __shared__ uint32_t s_min[4], s_max[4], s_big[4];
   __shared__ unsigned long long s_sum[4];
-  uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+  uint32_t mn = 0xFFFFFFFFu, mx = 0u, big = 0u;
   unsigned long long sum = 0;
   for (int b = threadIdx.x; b < nb; b += kBlock) {
     const uint4 q = part[b];
     mn = min(mn, q.x);
     mx = max(mx, q.y);
+    big = max(big, q.w ? 0xFFFFFFFFu : q.z);
     sum += (unsigned long long)q.z | ((unsigned long long)q.w << 32);
   }
   for (int off = 32; off >= 1; off >>= 1) {
     mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
     mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    big = max(big, (uint32_t)__shfl_xor((int)big, off, 64));
     sum += __shfl_xor(sum, off, 64);
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) {
     s_min[wave] = mn;
     s_max[wave] = mx;
+    s_big[wave] = big;
     s_sum[wave] = sum;
   }
   __syncthreads();
+  big = max(max(s_big[0], s_big[1]), max(s_big[2], s_big[3]));
   if (threadIdx.x == 0) {
     sum = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
     stats[0] = min(min(s_min[0], s_min[1]), min(s_min[2], s_min[3]));
@@ -661,6 +685,7 @@ __device__ __forceinline__ void stats_reduce(const uint4* __restrict__ part, int
     stats[2] = (uint32_t)sum;
     stats[3] = (uint32_t)(sum >> 32);
   }
+  return (uint32_t)min((unsigned long long)big + sum / kDirectShare, 0xFFFFFFFFull);
 }
 
 // Keys of the visible (view, Gaussian) pairs only, in (view, Gaussian)
@@ -789,7 +814,7 @@ __global__ __launch_bounds__(kBlock) void k_stage1_close(
     uint32_t nchunk, uint32_t* __restrict__ stats, const gs_camera* __restrict__ cams, int V,
     uint32_t* __restrict__ seg_base, int32_t* __restrict__ txv, CrowdSample cs) {
   if (blockIdx.x > 3) {
-    crowd_count(cs, blockIdx.x - 4, stats + kCrowded);
+    crowd_count(cs, blockIdx.x - 4, stats + kLeaveDirect);
     return;
   }
   if (blockIdx.x == 3) {
@@ -797,7 +822,9 @@ __global__ __launch_bounds__(kBlock) void k_stage1_close(
     return;
   }
   if (blockIdx.x == 0) {
-    stats_reduce(part, (int)nchunk, stats);
+    const uint32_t cost = stats_reduce(part, (int)nchunk, stats);
+    if (threadIdx.x == 0 && cs.direct && cost > kDirectCost && atomicExch(cs.leave, 1u) == 0)
+      tell_host(stats + kLeaveDirect);
   } else {
     uint32_t* a = blockIdx.x == 1 ? vis : icnt;
     // 64 values per thread and round, or 4 where one round of them is enough
@@ -1041,12 +1068,12 @@ __device__ __forceinline__ uint32_t xcd_chunk() {
 }
 
 // rows[chunk of the view][tile]: instances per tile.  Grid: chunks by views.
-// Nothing happens in a crowded job, here and in the two kernels behind.
+// Nothing happens in a job that is left, here and in the two kernels behind.
 __global__ __launch_bounds__(kChunkThreads) void k_tile_count(
     int n, int ld, int V, const int32_t* __restrict__ tiles, uint32_t* __restrict__ splat_words,
     const uint32_t* __restrict__ seg_base, const int32_t* __restrict__ txv,
-    const uint32_t* __restrict__ crowded, uint32_t* __restrict__ rows) {
-  if (*crowded != 0) return;
+    const uint32_t* __restrict__ leave, uint32_t* __restrict__ rows) {
+  if (*leave != 0) return;
   __shared__ ChunkPairs sh;
   const uint32_t chunk = xcd_chunk();
   for (int v = blockIdx.y; v < V; v += gridDim.y) {
@@ -1074,10 +1101,10 @@ constexpr uint32_t kColumnRows = 16;
 
 __global__ __launch_bounds__(1024) void k_tile_columns(int V, uint32_t nseg, uint32_t chunks,
                                                        const uint32_t* __restrict__ seg_base,
-                                                       const uint32_t* __restrict__ crowded,
+                                                       const uint32_t* __restrict__ leave,
                                                        uint32_t* __restrict__ rows,
                                                        uint32_t* __restrict__ counts) {
-  if (*crowded != 0) return;
+  if (*leave != 0) return;
   __shared__ uint32_t s_sum[16][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t seg = blockIdx.x * 64 + lane;
@@ -1134,11 +1161,11 @@ constexpr int kScanBlock = 1024;
 
 __global__ __launch_bounds__(kScanBlock) void k_tile_scan(uint32_t* __restrict__ counts,
                                                           uint32_t nseg, uint64_t capacity,
-                                                          const uint32_t* __restrict__ crowded,
+                                                          const uint32_t* __restrict__ leave,
                                                           uint32_t* __restrict__ longest,
                                                           uint32_t* __restrict__ ready,
                                                           uint32_t* __restrict__ go) {
-  if (*crowded != 0) {  // the host knows and does not wait for this
+  if (*leave != 0) {  // the host knows and does not wait for this
     if (threadIdx.x == 0) *go = 0u;
     return;
   }
@@ -1786,9 +1813,10 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
   uint32_t* icnt = at<uint32_t>(ws, L.iparts);
   const DirectPlan d = plan_direct(p, L);
   const uint32_t nseg = (uint32_t)p.n_segments;
-  uint32_t* crowded = at<uint32_t>(ws, L.total) + 1;
+  uint32_t* leave = at<uint32_t>(ws, L.total) + 1;
   CrowdSample cs{};
-  cs.crowded = crowded;
+  cs.leave = leave;
+  cs.direct = d.possible;
   uint32_t sample_blocks = 0;
   if (d.possible && p.n > (int)kDirectLongest) {  // else no list can be longer
     // in the place of the rows of counts, which come later: at most 4 of the
@@ -1820,11 +1848,11 @@ hipError_t bin_sort_stage1(const BinSortPlan& p, const gs_projected& proj,
     uint32_t* rows = at<uint32_t>(ws, d.rows);
     hipLaunchKernelGGL(k_tile_count, dim3(gx, gy), dim3(kChunkThreads), 0, s, p.n, p.ld,
                        p.n_views, proj.tiles_touched, reinterpret_cast<uint32_t*>(proj.splat),
-                       at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), crowded, rows);
+                       at<uint32_t>(ws, L.seg_base), at<int32_t>(ws, L.txv), leave, rows);
     hipLaunchKernelGGL(k_tile_columns, dim3(cdiv(nseg, 64u)), dim3(1024), 0, s, p.n_views, nseg,
-                       gx, at<uint32_t>(ws, L.seg_base), crowded, rows, counts);
+                       gx, at<uint32_t>(ws, L.seg_base), leave, rows, counts);
     hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nseg,
-                       (uint64_t)p.capacity, crowded, stats + kLongest, stats + kCountsReady,
+                       (uint64_t)p.capacity, leave, stats + kLongest, stats + kCountsReady,
                        at<uint32_t>(ws, L.total));
   }
   return hipGetLastError();
