@@ -1932,14 +1932,37 @@ __global__ __launch_bounds__(256) void k_grad_gather(int n, int ld, int V,
 }  // namespace
 
 namespace {
-// Most tiles of a forward launch that runs one wave per quadrant.  render_fwd
-// stage with the L1 term, one wave per tile -> four, in us: 64 tiles 372 ->
-// 84, 1,200 tiles (0.65 M instances) 200 -> 71, 3,600 tiles (1.1 M) 148 ->
-// 93, 10,880 tiles 257 -> 202, 21,760 tiles 428 -> 385, 32,640 tiles 610 ->
-// 582, 54,400 tiles 958 -> 956, 108,800 tiles (32 M) 1,893 -> 1,898.  Where
-// they are equal the fourfold staging is work for nothing (the backward that
-// follows such a launch ran 3 % slower), so the line lies below that.
-constexpr int kQuadFwdTiles = 36000;
+// What a launch's lists look like, as far as the host knows.
+struct ListShape {
+  double mean;    // instances per tile
+  double spread;  // tiles per (view, Gaussian) pair
+};
+
+ListShape shape_of(const gs_projected& proj, const gs_tile_lists& lists, int V, int tiles) {
+  const double M = (double)lists.count;
+  return {M / std::max(tiles, 1), M / std::max((double)proj.n * V, 1.0)};
+}
+
+// Forward launches that run one wave per quadrant.  render_fwd stage with the
+// L1 term, one wave per tile -> four, in us: 64 tiles 372 -> 84, 1,200 tiles
+// (0.65 M instances) 200 -> 71, 3,600 tiles (1.1 M) 148 -> 93, 10,880 tiles 257
+// -> 202, 21,760 tiles 428 -> 385, 32,640 tiles 610 -> 582, 54,400 tiles 958 ->
+// 956, 108,800 tiles (32 M) 1,893 -> 1,898.  Where they are equal the fourfold
+// staging is work for nothing (the backward that follows such a launch ran 3 %
+// slower).  It stops paying earlier where the waves have nothing to share out:
+// lists of 4 entries 14 -> 15 us at 7,200 tiles, 26 -> 35 at 21,600; and where
+// splats are wide, so that an entry concerns all four quadrants: of 39 tiles a
+// splat 0.95 times at 14,400 tiles, 1.07 at 21,600 and 1.13 at 36,000, of 9
+// 0.87, 0.94 and 1.04.  One view of 3840x2160 (32,400 tiles) 1.01-1.22 times.
+constexpr int kQuadFwdAll = 4000, kQuadFwdMost = 12000, kQuadFwdNarrow = 30000;
+constexpr double kQuadFwdMean = 40.0, kQuadFwdSpread = 20.0;
+
+bool quads_fwd(int tiles, const ListShape& sh) {
+  if (tiles <= kQuadFwdAll) return true;
+  return sh.mean >= kQuadFwdMean &&
+         (tiles <= kQuadFwdMost || (tiles <= kQuadFwdNarrow && sh.spread <= kQuadFwdSpread));
+}
+
 // The same for a batch of requests (no backward follows, uneven sizes): 14,160
 // tiles 364 -> 279, 30,720 tiles 532 -> 513, 66,000 tiles 1,102 -> 1,072,
 // 134,400 tiles 1,955 -> 2,073.
@@ -1963,13 +1986,27 @@ constexpr int kOctTiles = 640;
 // tiles 60.1 -> 58.3 us, 3,813 tiles 54.0 -> 50.9, 7,752 tiles 125.3 -> 123.7,
 // 32,640 tiles 550 -> 560.
 constexpr int kL1OneTiles = 8192;
-// Most tiles of a backward launch that starts with its longest lists (beyond,
-// the last round of waves is a small part of the launch, and neighbouring
-// tiles share records in the L2s).  render_bwd with the ordering's launch, in
-// launch order -> longest first, in us: 1,200 tiles (0.65 M instances) 165 ->
-// 156, 3,813 tiles 128 -> 105, 7,752 tiles 301 -> 260, 16,320 tiles 562 -> 555,
-// 32,640 tiles 1,031 -> 1,016, 54,400 tiles 1,620 -> 1,649.
-constexpr int kOrderTiles = 36000;
+// Backward launches that start with their longest lists.  render_bwd with the
+// ordering's launch, in launch order -> longest first, in us: 1,200 tiles (0.65
+// M instances) 165 -> 156, 3,813 tiles 128 -> 105, 7,752 tiles 301 -> 260,
+// 16,320 tiles 562 -> 555.  Beyond some rounds of waves the last one is a small
+// part of the launch, and neighbouring tiles no longer share records and rows
+// in the L2s: 30,000 tiles are the line where the gain is left to noise.  It
+// pays where a list's length says what its tile costs, so not with short lists
+// (mean of 4: 39 -> 47 at 2,400 tiles, 133 -> 170 at 28,800; of 60: 0.79 times
+// at 3,813, 1.05 at 14,400), nor with long ones, which most pixels leave early
+// (mean of 1,000: 1.11 at 7,200; of 430: 0.99 there and 1.05 at 28,800) unless
+// a splat has few tiles (2.2: 0.77 at 6,144 with a mean of 3,400), nor with wide
+// splats (39 tiles a splat: 1.08 at 10,800); else 0.76-0.95.
+constexpr int kOrderTiles = 30000, kOrderFew = 8192;
+constexpr double kOrderSpread = 30.0, kOrderSmall = 3.0;
+
+bool longest_first(int tiles, const ListShape& sh) {
+  const bool few = tiles <= kOrderFew;
+  return tiles > kOctTiles && tiles <= kOrderTiles && sh.spread <= kOrderSpread &&
+         sh.mean >= (few ? 20.0 : 80.0) &&
+         (sh.mean <= (few ? 600.0 : 400.0) || (few && sh.spread <= kOrderSmall));
+}
 }  // namespace
 
 void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int V, int W, int H,
@@ -1990,7 +2027,7 @@ void launch_render_fwd(const gs_projected& proj, const gs_tile_lists& lists, int
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, g_work);
-  else if (blocks <= kQuadFwdTiles)
+  else if (quads_fwd(blocks, shape_of(proj, lists, V, blocks)))
     hipLaunchKernelGGL(blocks <= kOctTiles ? k_render_fwd_octs<false> : k_render_fwd_quads<false>,
                        dim3(blocks), dim3(blocks <= kOctTiles ? 512 : 256), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
@@ -2025,7 +2062,7 @@ void launch_render_fwd_l1(const gs_projected& proj, const gs_tile_lists& lists, 
                        reinterpret_cast<const uint2*>(lists.ranges), W, H, TX, tpv, bg[0], bg[1],
                        bg[2], image, final_T, n_contrib, target, grad, (float)(1.0 / count),
                        partial, g_work);
-  else if (blocks <= kQuadFwdTiles)
+  else if (quads_fwd(blocks, shape_of(proj, lists, V, blocks)))
     hipLaunchKernelGGL(blocks <= kOctTiles ? k_render_fwd_octs<true> : k_render_fwd_quads<true>,
                        dim3(blocks), dim3(blocks <= kOctTiles ? 512 : 256), 0, s,
                        reinterpret_cast<const float4*>(proj.splat), proj.ld, lists.vals,
@@ -2092,7 +2129,7 @@ void launch_render_bwd(const gs_projected& proj, const gs_tile_lists& lists, int
     const bool octs = blocks <= kOctTiles, quads = blocks <= kQuadBwdTiles;
     // the order lies in grad2d, which is written after this launch
     uint32_t* order = nullptr;
-    if (!octs && blocks <= kOrderTiles &&
+    if (longest_first(blocks, shape_of(proj, lists, V, blocks)) &&
         (size_t)blocks <= (size_t)kGrad2dFloats * proj.ld * (size_t)V) {
       order = reinterpret_cast<uint32_t*>(grad2d);
       hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(kOrderThreads), 0, s,
