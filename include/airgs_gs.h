@@ -262,9 +262,9 @@ const char* gs_stage_name(int stage);
  *   7 bwd pairs inside the pixel's list prefix with alpha >= 1/255.
  * The backward counts in the kernel that the launch would run; where that
  * evaluates half quadrants (up to 640 tiles), 6 counts the quadrants.  The
- * forward counts in the kernel of one wave per tile at every size: up to
- * 36,000 tiles, where others run, its counters are the path's work and not
- * the running kernel's, and do not go with its times.
+ * forward counts in the kernel of one wave per tile at every size: where
+ * others run (launches of up to 30,000 tiles) its counters are the path's
+ * work and not the running kernel's, and do not go with its times.
  * The counting kernels are slower (one 64-bit atomic per counter per tile)
  * and are meant for runs outside any timed region.  NULL switches counting
  * off.  Other calls ignore the setting. */

@@ -297,7 +297,7 @@ class Context:
         """counters: a zeroed int64 device tensor of WORK_COUNTERS values that
         the render calls of this context add their work tallies to, or None
         to switch counting off.  The forward counts in the one-wave kernel,
-        also where launches of up to 36,000 tiles run others."""
+        also where launches of up to 30,000 tiles run others."""
         if counters is not None:
             assert counters.dtype == torch.int64 and counters.numel() >= WORK_COUNTERS
         self.check(self.lib.gs_set_work_counters(self.handle, _ptr(counters)))
